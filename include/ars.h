@@ -218,10 +218,10 @@ int ars_step(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, int n_s
 
 /* For callers that cannot allocate device memory (code under graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): ars_step
- * without d_tmp and d_work.  Its scratch -- the 256-byte control block
- * (CFL rate slots, fault latch) and the ping-pong state -- is a static
+ * without d_tmp and d_work.  Its scratch -- the 2 KiB control block
+ * (CFL rate maxima, fault latch) and the ping-pong state -- is a static
  * device array of the library, one per GPU, held until the process ends:
- * 256 + 8 * ARS_NOALLOC_MAX_STATE bytes (about 1 MiB).  The call allocates
+ * 2048 + 8 * ARS_NOALLOC_MAX_STATE bytes (about 1 MiB).  The call allocates
  * nothing.  Returns ARS_ESCRATCH, launching nothing, when
  * ars_state_len(ctx) > ARS_NOALLOC_MAX_STATE (e.g. 2D grids up to 256 x 128
  * fit; larger problems use ars_step).  Results, *d_t, *d_dt and d_dt_log are

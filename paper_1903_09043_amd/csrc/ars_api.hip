@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -17,7 +18,7 @@
 
 namespace {
 
-constexpr size_t CTL_BYTES = 256;
+using ars::CTL_BYTES;
 
 int check(hipError_t e) { return e == hipSuccess ? ARS_OK : ARS_EDEVICE; }
 
@@ -666,7 +667,9 @@ int ars_fault(ars_ctx* ctx, void* d_work, int64_t* fault_cell, void* stream) {
   if (!ctx || !d_work) return ARS_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   ars::Control h{};
-  if (hipMemcpyAsync(&h, d_work, sizeof(ars::Control), hipMemcpyDeviceToHost, s) != hipSuccess) return ARS_EDEVICE;
+  // the latch lies before the rate maxima
+  if (hipMemcpyAsync(&h, d_work, offsetof(ars::Control, lammax), hipMemcpyDeviceToHost, s) != hipSuccess)
+    return ARS_EDEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return ARS_EDEVICE;
   if (fault_cell) *fault_cell = h.fault ? (int64_t)h.fault_cell : -1;
   if (h.fault) {

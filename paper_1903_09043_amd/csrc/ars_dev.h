@@ -31,15 +31,27 @@ struct Params {
   int nc;               // 1: non-conservative energy scheme (App. B)
 };
 
-// Workspace control block (first 256 bytes of the workspace).
+// A maximum rate is kept as RATE_WORDS partial maxima (FP64 bits; rates are
+// >= 0, so the bits order as the values): workgroup b folds its own into
+// word b mod RATE_WORDS and the reader takes the maximum of the words.
+// Atomics on ONE word are served in turn, 14 ns each on MI355X whatever they
+// find there: 1850 one-wave workgroups that end together (2D, 1024^2) waited
+// 13-16 us of a 41 us step, 2048 blocks 25 us of k_rate's 30.
+constexpr int RATE_WORDS = 64;
+struct RateMax {
+  unsigned long long w[RATE_WORDS];
+};
+
+// Workspace control block (first CTL_BYTES bytes of the workspace).
 struct Control {
-  unsigned long long lammax[4];   // max rate slots (FP64 bits; rates are >= 0)
   unsigned long long fault_cell;  // min faulting cell (ULLONG_MAX = none)
   unsigned int fault;             // latched flag
   unsigned int pad0;
-  double t_scratch;
-  unsigned long long pad1[25];
+  unsigned long long pad1[30];
+  RateMax lammax[3];              // rotating: step s reads s % 3, writes s + 1, clears s + 2
 };
+constexpr size_t CTL_BYTES = 2048;
+static_assert(sizeof(Control) <= CTL_BYTES, "control block exceeds its slot");
 
 #ifndef ARS_FASTMATH
 #define ARS_FASTMATH 1
@@ -206,8 +218,53 @@ __device__ __forceinline__ int resolve_lat(int r, int n, const int* bc) {
   return r < 0 ? 0 : n - 1;
 }
 
-__device__ __forceinline__ void atomic_max_rate(unsigned long long* slot, double v) {
-  atomicMax(slot, (unsigned long long)__double_as_longlong(v));
+__device__ __forceinline__ void atomic_max_rate(RateMax* m, double v) {
+  atomicMax(&m->w[blockIdx.x % RATE_WORDS], (unsigned long long)__double_as_longlong(v));
+}
+
+// v moved between the lanes of each row of 16 (DPP control CTRL): a register
+// move of the vector unit, a tenth of an LDS permute's latency.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+enum { DPP_ROW_ROR = 0x120 };  // + n: rotate right by n within the row
+
+__device__ __forceinline__ double larger(double a, double b) { return b > a ? b : a; }
+
+// v of lane `lane` (a literal), as a scalar.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Largest v of each full row of 16 lanes, in all of its lanes.
+__device__ __forceinline__ double row_max(double v) {
+  v = larger(v, dpp_move<DPP_ROW_ROR + 8>(v));
+  v = larger(v, dpp_move<DPP_ROW_ROR + 4>(v));
+  v = larger(v, dpp_move<DPP_ROW_ROR + 2>(v));
+  return larger(v, dpp_move<DPP_ROW_ROR + 1>(v));
+}
+
+// Largest v of a full wave, in all of its lanes.
+__device__ __forceinline__ double wave_max(double v) {
+  v = row_max(v);
+  return larger(larger(lane_value(v, 0), lane_value(v, 16)), larger(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// Maximum of the words, in every lane.  Each wave reads them for itself: four
+// words a lane of its first row of 16, which a partial last wave holds too.
+__device__ __forceinline__ double rate_of(const RateMax* m) {
+  static_assert(RATE_WORDS == 64, "four words per lane of a row");
+  const unsigned long long* w = m->w + 4 * (threadIdx.x & 15);
+  double v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = __longlong_as_double((long long)w[k]);
+  return lane_value(row_max(larger(larger(v[0], v[1]), larger(v[2], v[3]))), 0);
 }
 
 }  // namespace ars

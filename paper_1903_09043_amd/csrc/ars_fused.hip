@@ -34,22 +34,24 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
   using Ly = FusedLayout<DIM>;
   __shared__ double sm[Ly::TOTAL * NPOS];
   constexpr int NW = (NPOS + 63) / 64;  // waves (the last one partial if 64 does not divide NPOS)
-  __shared__ double red[NW];
 
   const int tid = threadIdx.x;
   // time step of this step
   double dt;
   if (io.rate_in)
-    dt = P.cfl / __longlong_as_double((long long)*io.rate_in);
+    dt = P.cfl / rate_of(io.rate_in);
   else
     dt = *io.dt_in;
   const double lamx = dt / P.dx[0];
   const double lamy = (DIM == 3) ? dt / P.dx[1] : 0.0;
   const double lamz = dt / P.dx[2];
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
-    if (io.clear_slot) *io.clear_slot = 0ull;
-    if (io.t) *io.t = *io.t + dt;
-    if (io.dt_log) *io.dt_log = dt;
+  if (blockIdx.x == 0) {
+    static_assert(NPOS >= RATE_WORDS, "one thread clears one word");
+    if (io.clear_slot && tid < RATE_WORDS) io.clear_slot->w[tid] = 0ull;
+    if (tid == 0) {
+      if (io.t) *io.t = *io.t + dt;
+      if (io.dt_log) *io.dt_log = dt;
+    }
   }
 
   // Persistent balanced schedule: the (tile, plane) pairs are laid end to
@@ -80,31 +82,21 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
     atomicMin(&io.ctl->fault_cell, badcell);
   }
   if (io.rate_out) {
-    double m = lmax;
-    if (NPOS % 64 != 0) {
-      // a partial last wave has no lanes past NPOS to shuffle with: gather
-      // every position's rate into wave 0 through LDS (free after the march)
+    double m;
+    if (NW == 1) {
+      m = wave_max(lmax);  // no barrier, no LDS: the tail of a one-wave workgroup is on every 2D step
+    } else {
+      // every position's rate to wave 0 through LDS (free after the march)
       __syncthreads();
       sm[tid] = lmax;
       __syncthreads();
       m = 0.0;
-      if (tid < 64)
-        for (int j = tid; j < NPOS; j += 64) m = sm[j] > m ? sm[j] : m;
-    }
-    if (NPOS % 64 == 0 || tid < 64) {
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) {
-        const double o2 = __shfl_xor(m, off, 64);
-        m = o2 > m ? o2 : m;
+      if (tid < 64) {
+        for (int j = tid; j < NPOS; j += 64) m = larger(m, sm[j]);
+        m = wave_max(m);
       }
-      if ((tid & 63) == 0) red[tid >> 6] = m;
     }
-    __syncthreads();
-    if (tid == 0) {
-      double mm = red[0];
-      for (int w = 1; w < (NPOS % 64 == 0 ? NW : 1); ++w) mm = red[w] > mm ? red[w] : mm;
-      atomic_max_rate(io.rate_out, mm);
-    }
+    if (tid == 0) atomic_max_rate(io.rate_out, m);
   }
 }
 

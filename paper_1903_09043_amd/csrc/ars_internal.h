@@ -11,13 +11,13 @@ namespace ars {
 
 // Per-launch inputs/outputs of one fused step.
 struct StepIO {
-  const unsigned long long* rate_in;  // dt = cfl / rate (if non-null)
-  const double* dt_in;                // else dt = *dt_in
-  unsigned long long* rate_out;       // atomic max of the new state's rates (nullable)
-  unsigned long long* clear_slot;     // zeroed by one thread (slot used two steps later)
-  double* t;                          // t += dt (nullable)
-  double* dt_log;                     // dt written here (nullable)
-  Control* ctl;                       // fault latch
+  const RateMax* rate_in;  // dt = cfl / rate (if non-null)
+  const double* dt_in;     // else dt = *dt_in
+  RateMax* rate_out;       // atomic max of the new state's rates (nullable)
+  RateMax* clear_slot;     // zeroed by workgroup 0 (the maximum used two steps later; nullable)
+  double* t;               // t += dt (nullable)
+  double* dt_log;          // dt written here (nullable)
+  Control* ctl;            // fault latch
   int zchunk, ntx, nty;
 };
 
@@ -76,7 +76,7 @@ int batch_segments(const Params& P);
 int batch_default_zc(const Params& P, int rows);
 
 // Reductions (ars_reduce.hip).
-hipError_t launch_rate_reduce(const Params& P, const double* U, unsigned long long* slot, hipStream_t s);
+hipError_t launch_rate_reduce(const Params& P, const double* U, RateMax* slot, hipStream_t s);
 hipError_t launch_ctl_prep(Control* ctl, int mode, hipStream_t s);
 hipError_t launch_dt_finish(const Params& P, Control* ctl, int slot, double* d_dt, hipStream_t s);
 size_t diag_partial_bytes(const Params& P);

@@ -3,8 +3,8 @@
 // that cannot allocate device memory (code under graph capture, tight
 // serving loops).
 //
-// The scratch of ars_step is a 256-byte control block (rate slots for the
-// CFL maximum, fault latch) in the caller's workspace plus a second state
+// The scratch of ars_step is a control block (rate maxima for the CFL
+// condition, fault latch) in the caller's workspace plus a second state
 // buffer for the ping-pong of the march.  Here both live in `scratch`: the
 // control block first, then room for a ping-pong state of at most
 // ARS_NOALLOC_MAX_STATE doubles.  The kernels are those of ars_step.
@@ -23,9 +23,8 @@
 
 namespace {
 
-constexpr size_t CTL_BYTES = 256;
+using ars::CTL_BYTES;
 constexpr size_t SCRATCH_BYTES = CTL_BYTES + (size_t)ARS_NOALLOC_MAX_STATE * sizeof(double);
-static_assert(sizeof(ars::Control) <= CTL_BYTES, "control block exceeds its slot");
 
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
@@ -48,11 +47,11 @@ int scratch_ptr(void** out) {
   return ARS_OK;
 }
 
-// Whole control block to its start values: rate slots 0, no fault.  A kernel
+// Whole control block to its start values: rate maxima 0, no fault.  A kernel
 // rather than a memset, so that the call can be captured in a graph.
-__global__ void k_noalloc_prep(ars::Control* ctl) {
+__global__ void __launch_bounds__(ars::RATE_WORDS) k_noalloc_prep(ars::Control* ctl) {
+  for (int i = 0; i < 3; ++i) ctl->lammax[i].w[threadIdx.x] = 0ull;
   if (threadIdx.x == 0) {
-    for (int i = 0; i < 4; ++i) ctl->lammax[i] = 0ull;
     ctl->fault = 0u;
     ctl->fault_cell = ~0ull;
   }
@@ -60,8 +59,8 @@ __global__ void k_noalloc_prep(ars::Control* ctl) {
 
 // Next dt from the last step's rate slot, NaN if a fault was latched.
 __global__ void k_noalloc_finish(double cfl, const ars::Control* ctl, int slot, double* d_dt) {
-  if (threadIdx.x == 0)
-    *d_dt = ctl->fault ? __builtin_nan("") : cfl / __longlong_as_double((long long)ctl->lammax[slot]);
+  const double r = ars::rate_of(&ctl->lammax[slot]);
+  if (threadIdx.x == 0) *d_dt = ctl->fault ? __builtin_nan("") : cfl / r;
 }
 
 }  // namespace
@@ -77,7 +76,7 @@ extern "C" int ars_step_noalloc(ars_ctx* ctx, double* d_state, int n, double* d_
   hipStream_t s = (hipStream_t)stream;
   ars::Control* ctl = (ars::Control*)base;
   double* tmp = (double*)((char*)base + CTL_BYTES);
-  hipLaunchKernelGGL(k_noalloc_prep, dim3(1), dim3(64), 0, s, ctl);
+  hipLaunchKernelGGL(k_noalloc_prep, dim3(1), dim3(ars::RATE_WORDS), 0, s, ctl);
   if (hipGetLastError() != hipSuccess) return ARS_EDEVICE;
   double* src = d_state;
   double* dst = tmp;

@@ -7,7 +7,7 @@
 namespace ars {
 
 template <int DIM>
-__global__ void __launch_bounds__(256) k_rate(Params P, const double* __restrict__ U, unsigned long long* slot) {
+__global__ void __launch_bounds__(256) k_rate(Params P, const double* __restrict__ U, RateMax* slot) {
   constexpr int NV = DIM + 2;
   __shared__ double red[4];
   double m = 0.0;
@@ -20,11 +20,7 @@ __global__ void __launch_bounds__(256) k_rate(Params P, const double* __restrict
     const double l = cell_rate<DIM>(P, q);
     m = l > m ? l : m;
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double o = __shfl_xor(m, off, 64);
-    m = o > m ? o : m;
-  }
+  m = wave_max(m);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -34,7 +30,7 @@ __global__ void __launch_bounds__(256) k_rate(Params P, const double* __restrict
   }
 }
 
-hipError_t launch_rate_reduce(const Params& P, const double* U, unsigned long long* slot, hipStream_t s) {
+hipError_t launch_rate_reduce(const Params& P, const double* U, RateMax* slot, hipStream_t s) {
   long long nb = (P.ncell + 255) / 256;
   if (nb > 2048) nb = 2048;
   if (P.dim == 3)
@@ -44,28 +40,27 @@ hipError_t launch_rate_reduce(const Params& P, const double* U, unsigned long lo
   return hipGetLastError();
 }
 
-// mode 0: clear rate slots 0..3; mode 1: clear slots 1..3 (keep slot 0);
-// mode 2: clear the fault latch.  A kernel, not a memset, so the call can
-// sit inside a captured graph.
-__global__ void k_ctl_prep(Control* ctl, int mode) {
-  if (threadIdx.x == 0) {
-    if (mode == 0 || mode == 1) {
-      for (int i = (mode == 0 ? 0 : 1); i < 4; ++i) ctl->lammax[i] = 0ull;
-    }
-    if (mode == 2) {
-      ctl->fault = 0u;
-      ctl->fault_cell = ~0ull;
-    }
+// mode 0: clear the rate maxima; mode 1: all but the first; mode 2: clear
+// the fault latch.  A kernel, not a memset, so the call can sit inside a
+// captured graph.
+__global__ void __launch_bounds__(RATE_WORDS) k_ctl_prep(Control* ctl, int mode) {
+  if (mode == 0 || mode == 1) {
+    for (int i = mode; i < 3; ++i) ctl->lammax[i].w[threadIdx.x] = 0ull;
+  }
+  if (mode == 2 && threadIdx.x == 0) {
+    ctl->fault = 0u;
+    ctl->fault_cell = ~0ull;
   }
 }
 
 hipError_t launch_ctl_prep(Control* ctl, int mode, hipStream_t s) {
-  hipLaunchKernelGGL(k_ctl_prep, dim3(1), dim3(64), 0, s, ctl, mode);
+  hipLaunchKernelGGL(k_ctl_prep, dim3(1), dim3(RATE_WORDS), 0, s, ctl, mode);
   return hipGetLastError();
 }
 
 __global__ void k_dt_finish(double cfl, const Control* ctl, int slot, double* d_dt) {
-  if (threadIdx.x == 0) *d_dt = cfl / __longlong_as_double((long long)ctl->lammax[slot]);
+  const double r = rate_of(&ctl->lammax[slot]);
+  if (threadIdx.x == 0) *d_dt = cfl / r;
 }
 
 hipError_t launch_dt_finish(const Params& P, Control* ctl, int slot, double* d_dt, hipStream_t s) {
