@@ -62,8 +62,6 @@ template <bool LM, bool DISS, bool NC, int EX, int EY>
 __global__ void __launch_bounds__(EX* EY) k_batch(BatchInst* insts, const Params* __restrict__ params,
                                                   const int* __restrict__ order, int nsteps) {
   constexpr int NPOS = EX * EY;
-  using Ly = FusedLayout<2>;
-  __shared__ double sm[Ly::TOTAL * NPOS];
   __shared__ double red[NPOS / 64];
   __shared__ unsigned long long badsh;
   const int k = order[blockIdx.x];
@@ -100,7 +98,7 @@ __global__ void __launch_bounds__(EX* EY) k_batch(BatchInst* insts, const Params
       const bool live = u < units;
       const int tx = live ? u % nxs : nxs;  // past the last segment: no output
       const int zs = live ? (u / nxs) * chunk : 0;
-      march_tile<2, LM, DISS, NC, EX, EY>(P, src, dst, sm, tx, 0, zs, 0, chunk, lamx, 0.0, lamz, lmax, bad);
+      march_tile<2, LM, DISS, NC, EX, EY>(P, src, dst, nullptr, tx, 0, zs, 0, chunk, lamx, 0.0, lamz, lmax, bad);
     }
     rate = block_max<NPOS>(lmax, red);  // its barriers complete the new state
     t = t + dt;

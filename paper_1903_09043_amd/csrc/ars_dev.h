@@ -222,8 +222,9 @@ __device__ __forceinline__ void atomic_max_rate(RateMax* m, double v) {
   atomicMax(&m->w[blockIdx.x % RATE_WORDS], (unsigned long long)__double_as_longlong(v));
 }
 
-// v moved between the lanes of each row of 16 (DPP control CTRL): a register
-// move of the vector unit, a tenth of an LDS permute's latency.
+// v moved between the lanes of the wave (DPP control CTRL): two register
+// moves of the vector unit, a tenth of an LDS access' latency.  Every lane
+// that another one reads has to be active.
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
   const long long b = __double_as_longlong(v);
@@ -231,7 +232,11 @@ __device__ __forceinline__ double dpp_move(double v) {
   const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-enum { DPP_ROW_ROR = 0x120 };  // + n: rotate right by n within the row
+enum {
+  DPP_ROW_ROR = 0x120,   // + n: rotate right by n within the row of 16
+  DPP_WAVE_SHL1 = 0x130, // from the next lane of the wave (0 in the last)
+  DPP_WAVE_SHR1 = 0x138  // from the previous lane of the wave (0 in the first)
+};
 
 __device__ __forceinline__ double larger(double a, double b) { return b > a ? b : a; }
 

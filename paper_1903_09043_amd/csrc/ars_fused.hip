@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
                                                        double* __restrict__ Uout, StepIO io) {
   constexpr int NPOS = EX * EY;
   using Ly = FusedLayout<DIM>;
-  __shared__ double sm[Ly::TOTAL * NPOS];
+  __shared__ double sm[DIM == 3 ? Ly::TOTAL * NPOS : 1];  // 2D exchanges through registers
   constexpr int NW = (NPOS + 63) / 64;  // waves (the last one partial if 64 does not divide NPOS)
 
   const int tid = threadIdx.x;
