@@ -228,6 +228,7 @@ int ars_create(const ars_config* cfg, ars_ctx** out) {
   c->P = derive(cfg);
   c->ts.tile3 = 0;
   c->ts.zchunk = ars::default_zchunk(c->P, 0);
+  c->ts.chosen = false;
   c->ts.num_cu = 0;
   c->ts.wg_per_cu = 0;
   c->len = (size_t)(cfg->dim + 2) * (size_t)c->P.ncell;
@@ -249,6 +250,7 @@ size_t ars_workspace_bytes_ref(const ars_ctx* c) { return c ? ars::ref_workspace
 int ars_set_zchunk(ars_ctx* c, int zchunk) {
   if (!c || zchunk < 1) return ARS_EINVAL;
   c->ts.zchunk = zchunk;
+  c->ts.chosen = true;
   return ARS_OK;
 }
 
@@ -257,6 +259,7 @@ int ars_get_zchunk(const ars_ctx* c) { return c ? c->ts.zchunk : -1; }
 int ars_set_tiling(ars_ctx* c, int zchunk, int wg_per_cu) {
   if (!c || zchunk < 1 || wg_per_cu < 0 || wg_per_cu > 32) return ARS_EINVAL;
   c->ts.zchunk = zchunk;
+  c->ts.chosen = true;
   c->ts.wg_per_cu = wg_per_cu;
   return ARS_OK;
 }
@@ -274,6 +277,7 @@ int ars_set_tile3(ars_ctx* c, int tile) {
   if (c->ts.tile3 != tile) {
     c->ts.tile3 = tile;
     c->ts.zchunk = ars::default_zchunk(c->P, tile);
+    c->ts.chosen = false;
   }
   return ARS_OK;
 }

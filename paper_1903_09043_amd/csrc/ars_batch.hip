@@ -98,7 +98,14 @@ __global__ void __launch_bounds__(EX* EY) k_batch(BatchInst* insts, const Params
       const bool live = u < units;
       const int tx = live ? u % nxs : nxs;  // past the last segment: no output
       const int zs = live ? (u / nxs) * chunk : 0;
-      march_tile<2, LM, DISS, NC, EX, EY>(P, src, dst, nullptr, tx, 0, zs, 0, chunk, lamx, 0.0, lamz, lmax, bad);
+      march_tile<2, LM, DISS, NC, EX, EY>(
+          P, src, dst, nullptr, tx, 0, zs, 0, chunk,
+          [&](double& lx, double& ly, double& lz) __attribute__((always_inline)) {
+            lx = lamx;
+            ly = 0.0;
+            lz = lamz;
+          },
+          lmax, bad);
     }
     rate = block_max<NPOS>(lmax, red);  // its barriers complete the new state
     t = t + dt;

@@ -263,13 +263,22 @@ __device__ __forceinline__ double wave_max(double v) {
 
 // Maximum of the words, in every lane.  Each wave reads them for itself: four
 // words a lane of its first row of 16, which a partial last wave holds too.
-__device__ __forceinline__ double rate_of(const RateMax* m) {
-  static_assert(RATE_WORDS == 64, "four words per lane of a row");
-  const unsigned long long* w = m->w + 4 * (threadIdx.x & 15);
+struct RateLoad {
   double v[4];
+  __device__ __forceinline__ void load(const RateMax* m) {
+    static_assert(RATE_WORDS == 64, "four words per lane of a row");
+    const unsigned long long* w = m->w + 4 * (threadIdx.x & 15);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = __longlong_as_double((long long)w[k]);
-  return lane_value(row_max(larger(larger(v[0], v[1]), larger(v[2], v[3]))), 0);
+    for (int k = 0; k < 4; ++k) v[k] = __longlong_as_double((long long)w[k]);
+  }
+  __device__ __forceinline__ double max() const {
+    return lane_value(row_max(larger(larger(v[0], v[1]), larger(v[2], v[3]))), 0);
+  }
+};
+__device__ __forceinline__ double rate_of(const RateMax* m) {
+  RateLoad r;
+  r.load(m);
+  return r.max();
 }
 
 }  // namespace ars

@@ -72,11 +72,13 @@ __device__ __forceinline__ bool wall_face_below(const Params& P, int q) {
 // segment of TX columns with its own tile and shift (plane p of the march
 // is plane zs + p of the grid), so a workgroup can advance several
 // segments or vertical chunks of one problem at once.
-template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY>
+// lam_of(lamx, lamy, lamz) gives dt / dx per axis; it is asked after the first
+// plane's loads have been issued, so that a time step still on its way from
+// memory does not hold them up.
+template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY, class LamOf>
 __device__ __forceinline__ void march_tile(const Params& P, const double* __restrict__ Uin,
                                            double* __restrict__ Uout, double* __restrict__ sm, const int tx,
-                                           const int ty, const int zs, const int z0, const int z1,
-                                           const double lamx, const double lamy, const double lamz,
+                                           const int ty, const int zs, const int z0, const int z1, LamOf&& lam_of,
                                            double& lmax, unsigned long long& badcell) {
   constexpr int NV = DIM + 2;
   constexpr int NPOS = EX * EY;
@@ -162,6 +164,8 @@ __device__ __forceinline__ void march_tile(const Params& P, const double* __rest
 #pragma unroll
     for (int v = 0; v < NV; ++v) Unx[v] = base[v * N];
   }
+  double lamx, lamy, lamz;
+  lam_of(lamx, lamy, lamz);
 
   // One plane of the march.  In 3D the loop below takes two planes per trip
   // so that the rotation of the vertical window between them is a renaming
@@ -546,7 +550,6 @@ __device__ __forceinline__ void march_tile(const Params& P, const double* __rest
   } else {
     for (; p <= z1 + 1; ++p) plane(p);
   }
-
 }
 
 }  // namespace ars

@@ -23,6 +23,8 @@
 //    the device and n steps need no host synchronisation.
 //  * No MFMA: nothing here is a contraction.
 
+#include <algorithm>
+
 #include "ars_fused.h"
 
 namespace ars {
@@ -36,44 +38,51 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
   constexpr int NW = (NPOS + 63) / 64;  // waves (the last one partial if 64 does not divide NPOS)
 
   const int tid = threadIdx.x;
-  // time step of this step
-  double dt;
+  // time step of this step: loaded here, used behind the first state loads
+  RateLoad rate{};
+  double dt_given = 0.0;
   if (io.rate_in)
-    dt = P.cfl / rate_of(io.rate_in);
+    rate.load(io.rate_in);
   else
-    dt = *io.dt_in;
-  const double lamx = dt / P.dx[0];
-  const double lamy = (DIM == 3) ? dt / P.dx[1] : 0.0;
-  const double lamz = dt / P.dx[2];
-  if (blockIdx.x == 0) {
+    dt_given = *io.dt_in;
+  double dt = 0.0;
+  auto lam_of = [&](double& lamx, double& lamy, double& lamz) __attribute__((always_inline)) {
+    dt = io.rate_in ? P.cfl / rate.max() : dt_given;
+    lamx = dt / P.dx[0];
+    lamy = (DIM == 3) ? dt / P.dx[1] : 0.0;
+    lamz = dt / P.dx[2];
+  };
+
+  // Persistent balanced schedule: the (tile, plane) pairs are laid end to
+  // end (tile-major) and every workgroup takes one contiguous share; shares
+  // of neighbouring workgroups on one XCD are neighbours in space, so halo
+  // re-reads hit that XCD's L2.  The shares are io.share pairs each, the
+  // first io.extra of them one more: 32-bit words (there are at most 2^31
+  // pairs) and no division here, where 64-bit quotients were 400 scalar
+  // instructions in front of the first load.
+  const unsigned G = gridDim.x, b = blockIdx.x;
+  const unsigned lw = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  unsigned cur = lw * io.share + min(lw, io.extra);
+  const unsigned stop = cur + io.share + (lw < io.extra ? 1u : 0u);
+  double lmax = 0.0;
+  unsigned long long badcell = ~0ull;
+  while (cur < stop) {
+    const int tile = (int)(cur / (unsigned)P.nz);
+    const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);
+    const int z1 = (int)min((unsigned)P.nz, (unsigned)z0 + (stop - cur));
+    cur += z1 - z0;
+    const int tx = (DIM == 3) ? tile % io.ntx : tile * EY + (int)threadIdx.x / EX;
+    const int ty = (DIM == 3) ? tile / io.ntx : 0;
+    march_tile<DIM, LM, DISS, NC, EX, EY>(P, Uin, Uout, sm, tx, ty, 0, z0, z1, lam_of, lmax, badcell);
+  }
+
+  if (b == 0) {
     static_assert(NPOS >= RATE_WORDS, "one thread clears one word");
     if (io.clear_slot && tid < RATE_WORDS) io.clear_slot->w[tid] = 0ull;
     if (tid == 0) {
       if (io.t) *io.t = *io.t + dt;
       if (io.dt_log) *io.dt_log = dt;
     }
-  }
-
-  // Persistent balanced schedule: the (tile, plane) pairs are laid end to
-  // end (tile-major) and every workgroup takes one contiguous share; shares
-  // of neighbouring workgroups on one XCD are neighbours in space, so halo
-  // re-reads hit that XCD's L2.
-  const long long total = (long long)io.ntx * io.nty * P.nz;
-  const int G = gridDim.x;
-  const int b = blockIdx.x;
-  const int lw = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-  long long cur = total * lw / G;
-  const long long stop = total * (lw + 1) / G;
-  double lmax = 0.0;
-  unsigned long long badcell = ~0ull;
-  while (cur < stop) {
-    const int tile = (int)(cur / P.nz);
-    const int z0 = (int)(cur % P.nz);
-    const int z1 = (int)min((long long)P.nz, (long long)z0 + (stop - cur));
-    cur += z1 - z0;
-    const int tx = (DIM == 3) ? tile % io.ntx : tile * EY + (int)threadIdx.x / EX;
-    const int ty = (DIM == 3) ? tile / io.ntx : 0;
-    march_tile<DIM, LM, DISS, NC, EX, EY>(P, Uin, Uout, sm, tx, ty, 0, z0, z1, lamx, lamy, lamz, lmax, badcell);
   }
 
   // ---- workgroup reduction of the new-state rate, fault latch --------------
@@ -110,7 +119,6 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
   constexpr int TY = (DIM == 3) ? EY - 4 : 1;
   io.ntx = (DIM == 3) ? (P.nx + TX - 1) / TX : (P.nx + TX * EY - 1) / (TX * EY);
   io.nty = (DIM == 3) ? (P.ny + TY - 1) / TY : 1;
-  io.zchunk = ts.zchunk;
   const long long total = (long long)io.ntx * io.nty * P.nz;
   // one workgroup per (CU x resident blocks), each with an equal share of
   // planes; never more workgroups than shares of at least zchunk planes
@@ -131,9 +139,19 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
       ncu = 256;
   }
   long long nwg = (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu;
-  const long long by_chunk = (total + ts.zchunk - 1) / ts.zchunk;
+  // 2D: up to one wave per SIMD (1024) a share is one plane, since the step
+  // is then the latency of one march; above that up to 4, and beyond some
+  // 12,000 pairs the number of resident waves decides.  Measured (us a step
+  // with shares of 1, 2, 4, 8): 256 x 128: 8.1, 8.4, 10.2, 14.3; 512 x 256:
+  // 12.3, 11.6, 11.6, 15.4; 1024 x 512: 19.6, 19.6, 19.6, 22.5; 1024^2: 24.6,
+  // 24.2, 24.1, 25.2; 2048 x 1024: 42.8, 41.2, 41.5, 41.3
+  long long least = ts.zchunk;
+  if (DIM == 2 && !ts.chosen) least = std::max(1ll, std::min({4ll, least, total / 1024}));
+  const long long by_chunk = (total + least - 1) / least;
   if (by_chunk < nwg) nwg = by_chunk;
   if (nwg < 1) nwg = 1;
+  io.share = (unsigned)(total / nwg);
+  io.extra = (unsigned)(total % nwg);
   hipLaunchKernelGGL((k_step_fused<DIM, LM, DISS, NC, EX, EY>), dim3((unsigned)nwg), dim3(EX * EY), 0, s, P, Uin, Uout,
                      io);
   return hipGetLastError();

@@ -18,7 +18,8 @@ struct StepIO {
   double* t;               // t += dt (nullable)
   double* dt_log;          // dt written here (nullable)
   Control* ctl;            // fault latch
-  int zchunk, ntx, nty;
+  unsigned share, extra;   // (tile, plane) pairs per workgroup, the first `extra` workgroups one more
+  int ntx, nty;
 };
 
 // Tiles of the 3D fused step (positions = outputs + the 2-cell halo on
@@ -29,6 +30,7 @@ constexpr int TILE3_EY[2] = {14, 24};
 struct TileShape {
   int tile3;      // 3D tile (index into TILE3_EX / TILE3_EY)
   int zchunk;     // minimum share of planes per workgroup
+  bool chosen;    // zchunk was set by the caller or the tuner (else 2D launches take a share of their own)
   int num_cu;     // compute units of the device (queried at first launch)
   int wg_per_cu;  // resident workgroups per CU of the chosen kernel
 };

@@ -118,6 +118,7 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
   if (cache_lookup(cache_path, key, &za, &wb, &ms, &tc) && za >= 1 && wb >= 0 && (tc == 0 || (tc == 1 && P.dim == 3))) {
     ctx->ts.tile3 = tc;
     ctx->ts.zchunk = za;
+    ctx->ts.chosen = true;
     ctx->ts.wg_per_cu = wb;
     r.tile3 = tc;
     r.zchunk = za;
@@ -155,6 +156,7 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
       for (int w : ws) {
         ctx->ts.tile3 = tl;
         ctx->ts.zchunk = z;
+        ctx->ts.chosen = true;
         ctx->ts.wg_per_cu = w;
         // every candidate starts from the caller's state
         if (hipMemcpyAsync(A, d_state, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) rc = ARS_EDEVICE;
