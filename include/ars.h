@@ -277,8 +277,9 @@ int ars_step_sched_to(ars_ctx* ctx, const double* d_in, double* d_a, double* d_b
  * u is eliminated (its rows are explicit in Pi) and the system for Pi,
  * rows scaled by 1 / (rho c^2), is solved to a relative residual tol: by
  * conjugate gradients when every axis is periodic or walled at both ends
- * (the operator is then symmetric positive definite), else (outflow) by
- * BiCGSTAB.  The acoustic dissipation of Pi* acts on u^n: with the
+ * (the operator is then symmetric positive definite), preconditioned by its
+ * constant-coefficient inverse (trigonometric transforms) where that takes
+ * less time, else (outflow) by BiCGSTAB.  The acoustic dissipation of Pi* acts on u^n: with the
  * low-Mach correction (theta ~ Ma) steps far above the acoustic limit are
  * stable, without it (theta = 1) only steps near it.  The
  * implicit (u*, Pi*) then enter the acoustic cell values, transport,

@@ -23,9 +23,10 @@
 // GPU layout: the reference step's padded workspace (primitives, explicit
 // faces for a, S, theta, then the implicit faces, L, b~, fluxes), padded
 // extensions of Pi and of the velocities it gives, and the vectors of an
-// unpreconditioned Krylov solver on the N unknowns Pi: conjugate gradients
-// when every axis is periodic or walled at both ends (the operator is then
-// symmetric positive definite), BiCGSTAB otherwise (outflow).  The operator is applied
+// Krylov solver on the N unknowns Pi: conjugate gradients when every axis is
+// periodic or walled at both ends (the operator is then symmetric positive
+// definite), plain or preconditioned by the constant-coefficient operator's
+// inverse (ars_trig.hip), BiCGSTAB otherwise (outflow).  The operator is applied
 // matrix-free: one kernel extends Pi to the ghost cells, one forms the
 // velocities of every padded cell from the Pi* of its two faces per axis
 // (ghosts by the boundary rules), one forms every row from the u* of the
@@ -41,6 +42,7 @@
 #include "ars_dev.h"
 #include "ars_internal.h"
 #include "ars_ref.h"
+#include "ars_trig.h"
 
 namespace ars {
 
@@ -53,7 +55,9 @@ constexpr int CG_CHECK = 16;  // CG iterations between host reads of the residua
 // scalar slots of the iteration
 enum { SC_RHO_OLD = 0, SC_ALPHA, SC_OMEGA, SC_RHO_NEW, SC_RV, SC_TS, SC_TT, SC_RR, SC_BB,
        SC_CG_RR,      // (r, r) of CG iterations 0, 2, 4, ... (SC_CG_RR + 1: 1, 3, 5, ...)
-       SC_CG_CHK = 11, SC_N = 16 };
+       SC_CG_CHK = 11,
+       SC_RANGE = 16,  // smallest and largest 1/(rho c^2), tau, 1/(rho c)
+       SC_DT = 22, SC_N = 32 };
 
 struct ImexLayout {
   RefGrid G;
@@ -426,22 +430,66 @@ __global__ void k_bicg_scalars(double* __restrict__ sc) {
 // device-scope fences (one per block, an L2 write-back each on a part whose
 // XCDs have L2s of their own), which cost far more.
 
+// Smallest (sign = 1) or largest (-1) v of a block, in every thread.
+__device__ __forceinline__ double block_extreme(double v, double sign) {
+  __shared__ double sh[BS / 64];
+  v = v * -sign;
+  v = wave_max(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  for (int w = 0; w < BS / 64; ++w) v = larger(v, sh[w]);
+  return v * -sign;
+}
+
 // Coefficients of the homogeneous operator per interior cell: tau, 1/(rho c)
-// and 1/(rho c^2) (the rows' scale), out of the padded workspace.
+// and 1/(rho c^2) (the rows' scale), out of the padded workspace, and each
+// block's smallest and largest of the three into part (six rows of gridDim).
 template <int DIM>
-__global__ void k_cg_coef(Params P, RefGrid G, const double* __restrict__ W, double* __restrict__ tau,
-                          double* __restrict__ irc, double* __restrict__ irc2) {
-  const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= P.ncell) return;
-  const int cx = (int)(c % P.nx);
-  const long long rr = c / P.nx;
-  const int cy = (int)(rr % P.ny);
-  const int cz = (int)(rr / P.ny);
-  const long long q = G.pad(cx + 2, DIM == 3 ? cy + 2 : 0, cz + 2);
+__global__ __launch_bounds__(BS) void k_cg_coef(Params P, RefGrid G, const double* __restrict__ W,
+                                                double* __restrict__ tau, double* __restrict__ irc,
+                                                double* __restrict__ irc2, double* __restrict__ part) {
   const long long n = G.npad;
-  tau[c] = W[R_R * n + q];
-  irc[c] = W[R_IRC * n + q];
-  irc2[c] = 1.0 / (W[R_RC * n + q] * W[R_C * n + q]);
+  const double inf = __builtin_huge_val();
+  double lo[3] = {inf, inf, inf}, hi[3] = {0.0, 0.0, 0.0};
+  for (unsigned c = blockIdx.x * BS + threadIdx.x; c < (unsigned)P.ncell; c += gridDim.x * BS) {
+    const unsigned rr = c / (unsigned)P.nx, cx = c - rr * (unsigned)P.nx;
+    const unsigned cz = DIM == 3 ? rr / (unsigned)P.ny : rr, cy = DIM == 3 ? rr - cz * (unsigned)P.ny : 0u;
+    const long long q = G.pad((int)cx + 2, DIM == 3 ? (int)cy + 2 : 0, (int)cz + 2);
+    const double v[3] = {1.0 / (W[R_RC * n + q] * W[R_C * n + q]), W[R_R * n + q], W[R_IRC * n + q]};
+    irc2[c] = v[0];
+    tau[c] = v[1];
+    irc[c] = v[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = v[k] < lo[k] ? v[k] : lo[k];
+      hi[k] = v[k] > hi[k] ? v[k] : hi[k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double a = block_extreme(lo[k], 1.0), b = block_extreme(hi[k], -1.0);
+    if (threadIdx.x == 0) {
+      part[(2 * k) * gridDim.x + blockIdx.x] = a;
+      part[(2 * k + 1) * gridDim.x + blockIdx.x] = b;
+    }
+  }
+}
+
+// The coefficients' ranges over the blocks, and the time step, for the host.
+__global__ __launch_bounds__(BS) void k_cg_range(const double* __restrict__ part, int nb, const double* __restrict__ d_dt,
+                                                 double* __restrict__ sc) {
+  for (int k = 0; k < 6; ++k) {
+    const double sign = k % 2 == 0 ? 1.0 : -1.0;
+    double v = part[k * nb];
+    for (int i = threadIdx.x; i < nb; i += BS) {
+      const double o = part[k * nb + i];
+      v = sign * o < sign * v ? o : v;
+    }
+    v = block_extreme(v, sign);
+    if (threadIdx.x == 0) sc[SC_RANGE + k] = v;
+  }
+  if (threadIdx.x == 0) sc[SC_DT] = *d_dt;
 }
 
 // Index offsets of the neighbours k - 2, k - 1, k + 1, k + 2 of coordinate
@@ -879,7 +927,7 @@ struct Imex {
     return hipGetLastError() == hipSuccess ? ARS_OK : ARS_EDEVICE;
   }
 
-  // Conjugate gradients on the same system (every side periodic).  The
+  // Conjugate gradients on the same system (every axis periodic or walled).  The
   // BiCGSTAB-only vectors hold the coefficients (rh: tau, sv: 1/(rho c),
   // t: 1/(rho c^2)) and b, once the first residual is formed, the second p.
   int solve_cg(double tol, int max_iter, int* its) {
@@ -903,23 +951,113 @@ struct Imex {
     // r = b - A x0 (also clears p and v, and copies r to rh, overwritten next)
     hipLaunchKernelGGL(k_bicg_start, dim3(nb), dim3(BS), 0, s, L.n, L.b, L.r, L.rh, L.p, L.v, L.sc);
     dot(L.b, L.b, SC_BB);
-    double bb = 0.0;
-    if (read(SC_BB, &bb) != ARS_OK) return ARS_EDEVICE;
-    const double target = tol * tol * (bb > 0.0 ? bb : 1.0);
     dot(L.r, L.r, SC_CG_RR);  // (r, r) of iteration 0
-    double rr0 = 0.0;
-    if (read(SC_CG_RR, &rr0) != ARS_OK) return ARS_EDEVICE;
+    const unsigned nc = nb < (unsigned)CG_BLOCKS ? nb : (unsigned)CG_BLOCKS;
+    hipLaunchKernelGGL(k_cg_coef<DIM>, dim3(nc), dim3(BS), 0, s, P, L.G, L.W, L.rh, L.sv, L.t, L.part);
+    hipLaunchKernelGGL(k_cg_range, dim3(1), dim3(BS), 0, s, L.part, (int)nc, d_dt, L.sc);
+    double h[SC_N];
+    if (hipMemcpyAsync(h, L.sc, SC_N * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return ARS_EDEVICE;
+    if (hipStreamSynchronize(s) != hipSuccess) return ARS_EDEVICE;
+    const double bb = h[SC_BB], rr0 = h[SC_CG_RR];
+    const double target = tol * tol * (bb > 0.0 ? bb : 1.0);
     if (!std::isfinite(rr0)) return ARS_ENOCONV;
     if (rr0 <= target) {
       if (its) *its = 0;
       return ARS_OK;
     }
-    hipLaunchKernelGGL(k_cg_coef<DIM>, dim3(nblk(P.ncell)), dim3(BS), 0, s, P, L.G, L.W, L.rh, L.sv, L.t);
+    TrigCoef tc;
+    if (prefer_trig(h, std::sqrt(rr0 / target), max_iter, &tc)) return iterate_trig(target, max_iter, its, tc, gb, wallmask);
     if constexpr (DIM == 2) {
       return iterate_2d(target, max_iter, its, ga, wallmask);
     } else {
       return iterate_3d(target, max_iter, its, ga, gb, wallmask);
     }
+  }
+
+  // Scratch of the trigonometric preconditioner: the reference workspace from
+  // L on holds nothing while the system is solved (cell values, fluxes).
+  double* trig_scratch() { return L.W + (size_t)R_L * L.G.npad; }
+  size_t trig_room() const { return (size_t)(R_NFIELD - R_L) * L.G.npad; }
+
+  // Whether conjugate gradients with the trigonometric preconditioner
+  // (ars_trig.hip) take less time than without, for a reduction of the
+  // residual by `red`, from what both need at most: with the condition
+  // number k of the iterated operator, log(2 red) / log((sqrt k + 1) /
+  // (sqrt k - 1)) iterations.  Preconditioned, k is at most the largest
+  // max/min ratio of the three coefficients (the reference values are their
+  // geometric means).  Without, k is the largest eigenvalue over the smallest
+  // and the bound more than what is seen (736 against 2300 at acoustic CFL 275
+  // on the 1024^2 vortex, 75 against 130 at CFL 30 on 64^2), so 0.4 of it is
+  // taken, and half a block of CG_CHECK iterations for the late read of the
+  // residual.  Time per iteration as measured (with the host's
+  // reads): without, 12.9 us at 64^2, 13.2 at 512^2, 27.8 at 1024^2 in 2D and
+  // 14 us at 32^3, 38 at 96^3; with, 68 us at 64^2 (the transforms' launches,
+  // product, updates and a read of the residual), 390 at 1024^2.
+  bool prefer_trig(const double* h, double red, int max_iter, TrigCoef* tc) const {
+    const double n = (double)L.n;
+    if (P.nx > TRIG_MAXN || P.ny > TRIG_MAXN || P.nz > TRIG_MAXN || (long long)P.ny * P.nz > (1 << 21) ||
+        trig_scratch_doubles(P) > trig_room())
+      return false;
+    double ratio = 1.0, ref[3];
+    for (int k = 0; k < 3; ++k) {
+      const double lo = h[SC_RANGE + 2 * k], hi = h[SC_RANGE + 2 * k + 1];
+      if (!(lo > 0.0) || !std::isfinite(hi)) return false;
+      ratio = std::fmax(ratio, hi / lo);
+      ref[k] = std::sqrt(lo * hi);
+    }
+    *tc = TrigCoef{ref[0], ref[1], ref[2]};
+    double top = h[SC_RANGE + 1];
+    for (int a = 0; a < 3; ++a) {
+      if (a == 1 && DIM == 2) continue;
+      const double lam = h[SC_DT] / P.dx[a];
+      top += lam * lam * h[SC_RANGE + 3] + 4.0 * lam * P.hK * h[SC_RANGE + 5];
+    }
+    auto most = [&](double k) {
+      const double s = std::sqrt(k);
+      return s > 1.0 + 1e-12 ? std::log(2.0 * red) / std::log((s + 1.0) / (s - 1.0)) : 1.0;
+    };
+    const double with = 2.0 + most(ratio), without = 8.0 + 0.4 * most(top / h[SC_RANGE]);
+    if (with > 0.5 * max_iter) return false;
+    const double TRIG_RATE = 35e6, MEM = 3.7e6;  // flop and bytes per us
+    double t_with = 35.0 + n * 150.0 / MEM;
+    for (int a = 0; a < 3; ++a) {
+      if (a == 1 && DIM == 2) continue;
+      const double len = a == 0 ? P.nx : (a == 1 ? P.ny : P.nz);
+      t_with += 2.0 * std::fmax(6.0, 2.0 * n * len / TRIG_RATE + n * 16.0 / MEM);
+    }
+    const double t_without = DIM == 2 ? std::fmax(12.5, 3.0 + n * 24e-6) : std::fmax(14.0, 6.0 + n * 36e-6);
+    return 20.0 + with * t_with < without * t_without;
+  }
+
+  // Preconditioned conjugate gradients: z = M^-1 r, then k_cg_apply with z in
+  // the place of r (p = z + beta p_old, q = A p; its beta and alpha come from
+  // the sums of (r, z)) and k_cg_xr; the host reads (r, r) every iteration,
+  // of which there are few.
+  int iterate_trig(double target, int max_iter, int* its, const TrigCoef& tc, unsigned gb, int wallmask) {
+    const int ps = CG_BLOCKS > DOT_BLOCKS ? CG_BLOCKS : DOT_BLOCKS;
+    double* const part_pq = L.part;
+    double* const part_rr = L.part + ps;
+    double* const part_rz = L.part + 2 * ps;
+    double* w = trig_scratch();
+    if (trig_setup(P, tc, d_dt, w, s) != hipSuccess) return ARS_EDEVICE;
+    double* pv[2] = {L.p, L.b};  // p = 0 on entry, so the first p is z
+    for (int it = 0; it < max_iter; ++it) {
+      const double* z = nullptr;
+      if (trig_solve(P, tc, L.r, w, &z, s) != hipSuccess) return ARS_EDEVICE;
+      hipLaunchKernelGGL(k_dot_partial, dim3(DOT_BLOCKS), dim3(BS), 0, s, L.r, z, L.n, part_rz);
+      if (it == 0) hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(BS), 0, s, part_rz, DOT_BLOCKS, L.sc + SC_CG_RR);
+      hipLaunchKernelGGL(k_cg_apply<DIM>, dim3(gb), dim3(BS), 0, s, P, d_dt, z, pv[it & 1], pv[(it + 1) & 1], L.rh,
+                         L.sv, L.t, L.v, part_rz, DOT_BLOCKS, part_pq, L.sc, it, wallmask);
+      hipLaunchKernelGGL(k_cg_xr, dim3(gb), dim3(BS), 0, s, L.n, pv[(it + 1) & 1], L.v, L.x, L.r, part_pq, (int)gb,
+                         part_rr, L.sc, it);
+      hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(BS), 0, s, part_rr, (int)gb, L.sc);
+      double rr = 0.0;
+      if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
+      if (its) *its = it + 1;
+      if (!std::isfinite(rr)) return ARS_ENOCONV;
+      if (rr <= target) return hipGetLastError() == hipSuccess ? ARS_OK : ARS_EDEVICE;
+    }
+    return ARS_ENOCONV;
   }
 
   // 3D: two kernels an iteration (k_cg_apply, k_cg_xr).
