@@ -15,6 +15,8 @@
 #include <cstring>
 #include <new>
 #include <numeric>
+#include <functional>
+#include <queue>
 #include <vector>
 
 #include "../../include/ars.h"
@@ -98,7 +100,7 @@ __global__ void __launch_bounds__(EX* EY) k_batch(BatchInst* insts, const Params
       const bool live = u < units;
       const int tx = live ? u % nxs : nxs;  // past the last segment: no output
       const int zs = live ? (u / nxs) * chunk : 0;
-      march_tile<2, LM, DISS, NC, EX, EY>(
+      march_tile<2, LM, DISS, NC, EX, EY, true>(
           P, src, dst, nullptr, tx, 0, zs, 0, chunk,
           [&](double& lx, double& ly, double& lz) __attribute__((always_inline)) {
             lx = lamx;
@@ -192,11 +194,46 @@ hipError_t launch_batch(ars_batch* b, void* table, int nsteps, hipStream_t s) {
   ars::BatchInst* insts = (ars::BatchInst*)base;
   const ars::Params* params = (const ars::Params*)(base + params_offset(b->n));
   const int* order = (const int*)(base + order_offset(b->n));
-  if (b->rows == 8)
+  if (b->run_rows == 8)
     launch_rows<8>(b, insts, params, order, nsteps, s);
   else
     launch_rows<4>(b, insts, params, order, nsteps, s);
   return hipGetLastError();
+}
+
+// Rows per workgroup of a batch whose tiling nobody has chosen: the smaller
+// makespan of the instances handed out largest first.  A CU holds 8 of these
+// waves (registers), so two workgroups of 4 rows or one of 8; a marched plane
+// costs a wave 1.0 us with its SIMD to itself and 1.25 us beside another (it
+// is issue bound), so 8 rows pay where a few large instances set the time and
+// 4 where there are enough of them.  Measured, 512 layers (64 x 32, 128 x 64
+// and 256 x 128 in equal parts), a step: 213 us with 4 rows, 191 with 8; 100
+// of them: 172 and 143.  (The marches are split; whole: 221 and 200, 199 and
+// 159.)
+double batch_makespan(const ars_batch* b, int rows) {
+  constexpr int CUS = 256, WAVES = 8;
+  const int slots = CUS * (WAVES / rows);
+  const bool alone = b->n * rows <= CUS * 4;  // at most one wave per SIMD
+  std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+  double last = 0.0;
+  for (int k : b->order) {
+    const int zc = ars::batch_default_zc(b->P[k], rows);
+    const long long units = (long long)ars::batch_segments(b->P[k]) * zc;
+    double t = (double)((units + rows - 1) / rows) * (double)(b->P[k].nz / zc + 4) * (alone ? 1.0 : 1.25);
+    if ((int)busy.size() >= slots) {
+      t += busy.top();
+      busy.pop();
+    }
+    busy.push(t);
+    last = std::max(last, t);
+  }
+  return last;
+}
+
+void choose_rows(ars_batch* b) {
+  b->run_rows = batch_makespan(b, 8) < batch_makespan(b, 4) ? 8 : 4;
+  b->run_zc.resize(b->n);
+  for (int k = 0; k < b->n; ++k) b->run_zc[k] = ars::batch_default_zc(b->P[k], b->run_rows);
 }
 
 void drop_graph(ars_batch* b) {
@@ -239,6 +276,7 @@ int ars_batch_create(int n_inst, const ars_config* cfgs, ars_batch** out) {
   std::iota(b->order.begin(), b->order.end(), 0);
   std::stable_sort(b->order.begin(), b->order.end(),
                    [&](int a, int c) { return b->P[a].ncell > b->P[c].ncell; });
+  choose_rows(b);
   *out = b;
   return ARS_OK;
 }
@@ -268,6 +306,8 @@ int ars_batch_set_tiling(ars_batch* b, int rows, const int* zc) {
   }
   b->rows = rows;
   for (int k = 0; k < b->n; ++k) b->zc[k] = zc ? zc[k] : ars::batch_default_zc(b->P[k], rows);
+  b->run_rows = b->rows;
+  b->run_zc = b->zc;
   drop_graph(b);
   return ARS_OK;
 }
@@ -294,7 +334,7 @@ int ars_batch_bind(ars_batch* b, double* d_states, double* d_tmps, void* d_table
     I.dt = 0.0;
     I.fault_cell = ~0ull;
     I.nxs = ars::batch_segments(b->P[k]);
-    I.zc = b->zc[k];
+    I.zc = b->run_zc[k];
     I.lm = b->P[k].low_mach;
     I.diss = b->P[k].diss;
     I.nc = b->P[k].nc;

@@ -29,7 +29,7 @@
 
 namespace ars {
 
-template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY>
+template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY, bool SPLIT>
 __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* __restrict__ Uin,
                                                        double* __restrict__ Uout, StepIO io) {
   constexpr int NPOS = EX * EY;
@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
     cur += z1 - z0;
     const int tx = (DIM == 3) ? tile % io.ntx : tile * EY + (int)threadIdx.x / EX;
     const int ty = (DIM == 3) ? tile / io.ntx : 0;
-    march_tile<DIM, LM, DISS, NC, EX, EY>(P, Uin, Uout, sm, tx, ty, 0, z0, z1, lam_of, lmax, badcell);
+    march_tile<DIM, LM, DISS, NC, EX, EY, SPLIT>(P, Uin, Uout, sm, tx, ty, 0, z0, z1, lam_of, lmax, badcell);
   }
 
   if (b == 0) {
@@ -112,6 +112,21 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 // Host-side launch
 // --------------------------------------------------------------------------
+// Resident workgroups per CU of one kernel.
+template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY, bool SPLIT>
+static int resident() {
+  static int occ = 0;
+  if (occ == 0) {
+    int o = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_step_fused<DIM, LM, DISS, NC, EX, EY, SPLIT>, EX * EY, 0) !=
+            hipSuccess ||
+        o < 1)
+      o = 1;
+    occ = o;
+  }
+  return occ;
+}
+
 template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY>
 static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uout, StepIO io, const TileShape& ts,
                                  hipStream_t s) {
@@ -120,17 +135,6 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
   io.ntx = (DIM == 3) ? (P.nx + TX - 1) / TX : (P.nx + TX * EY - 1) / (TX * EY);
   io.nty = (DIM == 3) ? (P.ny + TY - 1) / TY : 1;
   const long long total = (long long)io.ntx * io.nty * P.nz;
-  // one workgroup per (CU x resident blocks), each with an equal share of
-  // planes; never more workgroups than shares of at least zchunk planes
-  static int occ = 0;  // resident blocks per CU of this instance
-  if (occ == 0) {
-    int o = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_step_fused<DIM, LM, DISS, NC, EX, EY>, EX * EY, 0) !=
-            hipSuccess ||
-        o < 1)
-      o = 1;
-    occ = o;
-  }
   int ncu = ts.num_cu;
   if (ncu <= 0) {
     int dev = 0;
@@ -138,7 +142,6 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
       ncu = 256;
   }
-  long long nwg = (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu;
   // 2D: up to one wave per SIMD (1024) a share is one plane, since the step
   // is then the latency of one march; above that up to 4, and beyond some
   // 12,000 pairs the number of resident waves decides.  Measured (us a step
@@ -148,12 +151,24 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
   long long least = ts.zchunk;
   if (DIM == 2 && !ts.chosen) least = std::max(1ll, std::min({4ll, least, total / 1024}));
   const long long by_chunk = (total + least - 1) / least;
-  if (by_chunk < nwg) nwg = by_chunk;
-  if (nwg < 1) nwg = 1;
+  // one workgroup per (CU x resident blocks), each with an equal share of
+  // planes; never more workgroups than shares of at least that many planes
+  auto groups = [&](int occ) {
+    return std::max(1ll, std::min(by_chunk, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu));
+  };
+  long long nwg = groups(resident<DIM, LM, DISS, NC, EX, EY, false>());
+  // the split march where a share has enough steady planes (2D, us a step
+  // whole against split: 64 x 32, 5 planes marched: 6.9, 7.3; 1024^2, 10:
+  // 24.2, 23.4; 2048 x 1024, 15: 41.2, 38.4)
+  const bool split = DIM == 2 && total >= 6 * nwg;
+  if (split) nwg = groups(resident<DIM, LM, DISS, NC, EX, EY, DIM == 2>());
   io.share = (unsigned)(total / nwg);
   io.extra = (unsigned)(total % nwg);
-  hipLaunchKernelGGL((k_step_fused<DIM, LM, DISS, NC, EX, EY>), dim3((unsigned)nwg), dim3(EX * EY), 0, s, P, Uin, Uout,
-                     io);
+  const dim3 grid((unsigned)nwg), block(EX * EY);
+  if (split)
+    hipLaunchKernelGGL((k_step_fused<DIM, LM, DISS, NC, EX, EY, DIM == 2>), grid, block, 0, s, P, Uin, Uout, io);
+  else
+    hipLaunchKernelGGL((k_step_fused<DIM, LM, DISS, NC, EX, EY, false>), grid, block, 0, s, P, Uin, Uout, io);
   return hipGetLastError();
 }
 

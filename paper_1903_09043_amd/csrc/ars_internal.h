@@ -106,6 +106,8 @@ struct ars_batch {
   std::vector<ars_config> cfg;
   std::vector<ars::Params> P;
   std::vector<int> zc;        // vertical chunks per instance
+  int run_rows;               // what the launch takes: rows and zc once the caller or the tuner chose
+  std::vector<int> run_zc;    // them, the library's own choice until then
   std::vector<size_t> off;    // state offsets (doubles)
   std::vector<int> order;     // largest first
   size_t total;
