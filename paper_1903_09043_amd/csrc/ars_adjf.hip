@@ -85,14 +85,11 @@ static int adjf_num_cu() {
   return ncu;
 }
 
-// Workgroups of a march: `per_cu` per compute unit (at most 1024 in all, so
-// that the mu/kappa partials of V fit their slots), never more than
-// (tile, plane) pairs / 8.
-static int adjf_groups(const Params& P, int EX, int EY, int halo, int per_cu) {
-  const long long pairs = adjf_tiles(P, EX, EY, halo) * P.nz;
-  long long g = std::min(per_cu * adjf_num_cu(), 1024);
-  g = std::min(g, std::max(1ll, pairs / 8));
-  return (int)g;
+// Shares of a march (tile positions EX x EY, `halo` cells): one workgroup per
+// compute unit, at most 1024 so that the mu/kappa partials of V fit their
+// slots.
+static Shares adjf_shares(const Params& P, int EX, int EY, int halo) {
+  return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo);
 }
 
 // Share of workgroup b: workgroups are dealt to the 8 XCDs in turn, so the
@@ -334,6 +331,7 @@ struct AdjIOF {
   double* partial;     // mu/kappa partials, 2 per workgroup of V
   const double* dt;
   int ntx, nty;
+  Shares shares;
 };
 
 // nbar at a plane from lam^{n+1} (zero at wall ghosts, whose lam is zero)
@@ -618,15 +616,13 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_a(Params P, AdjIOF io) {
   __shared__ double sm[LA_TOTAL * EX * EY];
   const double dt = *io.dt;
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
-  const long long total = (long long)io.ntx * io.nty * P.nz;
-  const int G = gridDim.x, b = blockIdx.x;
-  const int lw = xcd_share(b, G);
-  long long cur = total * lw / G;
-  const long long stop = total * (lw + 1) / G;
+  const int b = blockIdx.x;
+  unsigned cur, stop;
+  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   while (cur < stop) {
-    const int tile = (int)(cur / P.nz);
-    const int z0 = (int)(cur % P.nz);
-    const int z1 = (int)min((long long)P.nz, (long long)z0 + (stop - cur));
+    const int tile = (int)(cur / (unsigned)P.nz);
+    const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);
+    const int z1 = (int)min((unsigned)P.nz, (unsigned)z0 + (stop - cur));
     cur += z1 - z0;
     adj_march_a<LM, EX, EY>(P, io, sm, tile % io.ntx, tile / io.ntx, z0, z1, lx, ly, lz);
     __syncthreads();
@@ -972,16 +968,14 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_v(Params P, AdjIOF io) {
   __shared__ double red[2][(NPOS + 63) / 64];
   const double dt = *io.dt;
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
-  const long long total = (long long)io.ntx * io.nty * P.nz;
-  const int G = gridDim.x, b = blockIdx.x;
-  const int lw = xcd_share(b, G);
-  long long cur = total * lw / G;
-  const long long stop = total * (lw + 1) / G;
+  const int b = blockIdx.x;
+  unsigned cur, stop;
+  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   double mu_acc = 0.0, ka_acc = 0.0;
   while (cur < stop) {
-    const int tile = (int)(cur / P.nz);
-    const int z0 = (int)(cur % P.nz);
-    const int z1 = (int)min((long long)P.nz, (long long)z0 + (stop - cur));
+    const int tile = (int)(cur / (unsigned)P.nz);
+    const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);
+    const int z1 = (int)min((unsigned)P.nz, (unsigned)z0 + (stop - cur));
     cur += z1 - z0;
     adj_march_v<EX, EY>(P, io, sm, tile % io.ntx, tile / io.ntx, z0, z1, lx, ly, lz, mu_acc, ka_acc);
     __syncthreads();
@@ -1251,15 +1245,13 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_b(Params P, AdjIOF io) {
   __shared__ double sm[LB_TOTAL * EX * EY];
   const double dt = *io.dt;
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
-  const long long total = (long long)io.ntx * io.nty * P.nz;
-  const int G = gridDim.x, b = blockIdx.x;
-  const int lw = xcd_share(b, G);
-  long long cur = total * lw / G;
-  const long long stop = total * (lw + 1) / G;
+  const int b = blockIdx.x;
+  unsigned cur, stop;
+  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   while (cur < stop) {
-    const int tile = (int)(cur / P.nz);
-    const int z0 = (int)(cur % P.nz);
-    const int z1 = (int)min((long long)P.nz, (long long)z0 + (stop - cur));
+    const int tile = (int)(cur / (unsigned)P.nz);
+    const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);
+    const int z1 = (int)min((unsigned)P.nz, (unsigned)z0 + (stop - cur));
     cur += z1 - z0;
     adj_march_b<LM, EX, EY>(P, io, sm, tile % io.ntx, tile / io.ntx, z0, z1, lx, ly, lz);
     __syncthreads();
@@ -1282,28 +1274,28 @@ static hipError_t adjf_t(const Params& P, const double* Un, const double* lam1, 
   // A: lam^n = lam^{n+1} + direct term; L, A, S-bar and face adjoints
   io.ntx = (P.nx + AF_AX - 5) / (AF_AX - 4);
   io.nty = (P.ny + AF_AY - 5) / (AF_AY - 4);
-  int g = adjf_groups(P, AF_AX, AF_AY, 2, 1);
-  hipLaunchKernelGGL((k_adjf_a<LM, AF_AX, AF_AY>), dim3((unsigned)g), dim3(AF_AX * AF_AY), 0, s, P, io);
+  io.shares = adjf_shares(P, AF_AX, AF_AY, 2);
+  hipLaunchKernelGGL((k_adjf_a<LM, AF_AX, AF_AY>), dim3(io.shares.groups), dim3(AF_AX * AF_AY), 0, s, P, io);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // V: + viscous and heat-flux terms, mu/kappa derivatives
   if (DISS) {
     io.ntx = (P.nx + AF_VX - 5) / (AF_VX - 4);
     io.nty = (P.ny + AF_VY - 5) / (AF_VY - 4);
-    g = adjf_groups(P, AF_VX, AF_VY, 2, 1);
-    hipLaunchKernelGGL((k_adjf_v<AF_VX, AF_VY>), dim3((unsigned)g), dim3(AF_VX * AF_VY), 0, s, P, io);
+    io.shares = adjf_shares(P, AF_VX, AF_VY, 2);
+    hipLaunchKernelGGL((k_adjf_v<AF_VX, AF_VY>), dim3(io.shares.groups), dim3(AF_VX * AF_VY), 0, s, P, io);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pgrad) {
-      e = launch_adj_params_final(g, io.partial, pgrad, s);
+      e = launch_adj_params_final((int)io.shares.groups, io.partial, pgrad, s);
       if (e != hipSuccess) return e;
     }
   }
   // B: + acoustic face-solver terms
   io.ntx = (P.nx + AF_BX - 3) / (AF_BX - 2);
   io.nty = (P.ny + AF_BY - 3) / (AF_BY - 2);
-  g = adjf_groups(P, AF_BX, AF_BY, 1, 1);
-  hipLaunchKernelGGL((k_adjf_b<LM, AF_BX, AF_BY>), dim3((unsigned)g), dim3(AF_BX * AF_BY), 0, s, P, io);
+  io.shares = adjf_shares(P, AF_BX, AF_BY, 1);
+  hipLaunchKernelGGL((k_adjf_b<LM, AF_BX, AF_BY>), dim3(io.shares.groups), dim3(AF_BX * AF_BY), 0, s, P, io);
   return hipGetLastError();
 }
 

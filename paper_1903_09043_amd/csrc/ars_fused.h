@@ -41,6 +41,16 @@ struct FusedLayout<2> {  // no LDS fields
   static constexpr int XA = 0, V = 0, DZ = 0, F = 0, B = 0, GX = 0, TOTAL = 0;
 };
 
+// First pair of workgroup `lw` in the pairs laid end to end (tile-major), and
+// one past its last: 32-bit words (there are at most 2^31 pairs) and one
+// 32-bit division, where 64-bit quotients were 400 scalar instructions in
+// front of the first load.
+__device__ __forceinline__ void share_of(const Shares& sh, unsigned lw, unsigned nz, unsigned& cur, unsigned& stop) {
+  const unsigned run = lw / sh.chunks, j = lw - run * sh.chunks;
+  cur = run * nz + j * sh.share + min(j, sh.extra);
+  stop = cur + sh.share + (j < sh.extra ? 1u : 0u);
+}
+
 // Vertical plane resolution: which plane to load and whether it is a wall
 // ghost (0 bottom, 1 top) built from that plane.
 __device__ __forceinline__ int plane_src(const Params& P, int q, int& ghost) {

@@ -53,17 +53,13 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
     lamz = dt / P.dx[2];
   };
 
-  // Persistent balanced schedule: the (tile, plane) pairs are laid end to
-  // end (tile-major) and every workgroup takes one contiguous share; shares
-  // of neighbouring workgroups on one XCD are neighbours in space, so halo
-  // re-reads hit that XCD's L2.  The shares are io.share pairs each, the
-  // first io.extra of them one more: 32-bit words (there are at most 2^31
-  // pairs) and no division here, where 64-bit quotients were 400 scalar
-  // instructions in front of the first load.
+  // Persistent schedule: every workgroup takes one contiguous share of the
+  // (tile, plane) pairs; those of one XCD are neighbours in space, so halo
+  // re-reads hit that XCD's L2.
   const unsigned G = gridDim.x, b = blockIdx.x;
   const unsigned lw = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
-  unsigned cur = lw * io.share + min(lw, io.extra);
-  const unsigned stop = cur + io.share + (lw < io.extra ? 1u : 0u);
+  unsigned cur, stop;
+  share_of(io.shares, lw, (unsigned)P.nz, cur, stop);
   double lmax = 0.0;
   unsigned long long badcell = ~0ull;
   while (cur < stop) {
@@ -112,6 +108,26 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 // Host-side launch
 // --------------------------------------------------------------------------
+Shares shares_of(long long tiles, int nz, long long most, long long least, int halo) {
+  const long long total = tiles * nz;
+  Shares a{};
+  a.groups = (unsigned)std::max(1ll, std::min((total + least - 1) / least, most));
+  a.chunks = a.groups;
+  a.share = (unsigned)(total / a.groups);
+  a.extra = (unsigned)(total % a.groups);
+  const long long longest = a.share + (a.extra ? 1 : 0);
+  const bool aligned = a.extra == 0 && (nz % longest == 0 || longest % nz == 0);
+  const long long marches = aligned ? (longest + nz - 1) / nz : 1 + (longest + nz - 2) / nz;
+  const long long c = std::min((long long)nz, std::min(most / tiles, std::max(1ll, nz / least)));
+  if (c < 1 || (nz + c - 1) / c + halo > longest + halo * marches) return a;
+  Shares b{};
+  b.groups = (unsigned)(tiles * c);
+  b.chunks = (unsigned)c;
+  b.share = (unsigned)(nz / c);
+  b.extra = (unsigned)(nz % c);
+  return b;
+}
+
 // Resident workgroups per CU of one kernel.
 template <int DIM, bool LM, bool DISS, bool NC, int EX, int EY, bool SPLIT>
 static int resident() {
@@ -150,21 +166,18 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
   // 24.2, 24.1, 25.2; 2048 x 1024: 42.8, 41.2, 41.5, 41.3
   long long least = ts.zchunk;
   if (DIM == 2 && !ts.chosen) least = std::max(1ll, std::min({4ll, least, total / 1024}));
-  const long long by_chunk = (total + least - 1) / least;
-  // one workgroup per (CU x resident blocks), each with an equal share of
-  // planes; never more workgroups than shares of at least that many planes
-  auto groups = [&](int occ) {
-    return std::max(1ll, std::min(by_chunk, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu));
+  // at most as many workgroups as are resident at once
+  const long long tiles = (long long)io.ntx * io.nty;
+  auto shares = [&](int occ) {
+    return shares_of(tiles, P.nz, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu, least, 4);
   };
-  long long nwg = groups(resident<DIM, LM, DISS, NC, EX, EY, false>());
+  io.shares = shares(resident<DIM, LM, DISS, NC, EX, EY, false>());
   // the split march where a share has enough steady planes (2D, us a step
   // whole against split: 64 x 32, 5 planes marched: 6.9, 7.3; 1024^2, 10:
   // 24.2, 23.4; 2048 x 1024, 15: 41.2, 38.4)
-  const bool split = DIM == 2 && total >= 6 * nwg;
-  if (split) nwg = groups(resident<DIM, LM, DISS, NC, EX, EY, DIM == 2>());
-  io.share = (unsigned)(total / nwg);
-  io.extra = (unsigned)(total % nwg);
-  const dim3 grid((unsigned)nwg), block(EX * EY);
+  const bool split = DIM == 2 && total >= 6ll * io.shares.groups;
+  if (split) io.shares = shares(resident<DIM, LM, DISS, NC, EX, EY, DIM == 2>());
+  const dim3 grid(io.shares.groups), block(EX * EY);
   if (split)
     hipLaunchKernelGGL((k_step_fused<DIM, LM, DISS, NC, EX, EY, DIM == 2>), grid, block, 0, s, P, Uin, Uout, io);
   else

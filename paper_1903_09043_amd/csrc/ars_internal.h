@@ -9,6 +9,21 @@
 
 namespace ars {
 
+// How the (tile, plane) pairs of a march along the vertical axis are shared
+// out: workgroup w takes chunk w % chunks of a run of tiles, `share` pairs,
+// the first `extra` chunks one more.  Whole: one run over all tiles (chunks =
+// groups), so every share is equal, but one that crosses from a tile to the
+// next starts a second march with its halo planes.  By tile: every tile is a
+// run of its own, no share crosses, the last chunk of a tile is shorter.
+struct Shares {
+  unsigned groups, chunks, share, extra;
+};
+
+// The schedule whose longest share marches fewer planes, halo planes of every
+// march counted, with at most `most` workgroups and at least `least` planes a
+// share where a tile has them.
+Shares shares_of(long long tiles, int nz, long long most, long long least, int halo);
+
 // Per-launch inputs/outputs of one fused step.
 struct StepIO {
   const RateMax* rate_in;  // dt = cfl / rate (if non-null)
@@ -18,7 +33,7 @@ struct StepIO {
   double* t;               // t += dt (nullable)
   double* dt_log;          // dt written here (nullable)
   Control* ctl;            // fault latch
-  unsigned share, extra;   // (tile, plane) pairs per workgroup, the first `extra` workgroups one more
+  Shares shares;           // schedule of the (tile, plane) pairs
   int ntx, nty;
 };
 
