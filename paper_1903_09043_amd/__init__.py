@@ -349,7 +349,7 @@ class Solver:
         return self
 
     def capture(self, n: int):
-        """Record n steps (one ars_step call: control preparation, n fused
+        """Record n steps (one ars_step call: n fused
         launches, the copy back after an odd count, the dt finish) into a
         graph on a capture stream.  Nothing runs while recording; every
         graph.replay() then advances this solver's state, t and dt by n

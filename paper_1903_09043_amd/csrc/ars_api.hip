@@ -484,7 +484,6 @@ int ars_step(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, int n, 
   if (n == 0) return ARS_OK;
   hipStream_t s = (hipStream_t)stream;
   ars::Control* ctl = ctl_of(d_work);
-  if (ars::launch_ctl_prep(ctl, 1, s) != hipSuccess) return ARS_EDEVICE;
   double* src = d_state;
   double* dst = d_tmp;
   for (int st = 0; st < n; ++st) {
@@ -539,7 +538,6 @@ int ars_step_to(ars_ctx* ctx, const double* d_in, double* d_a, double* d_b, doub
     return ARS_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   ars::Control* ctl = ctl_of(d_work);
-  if (ars::launch_ctl_prep(ctl, 1, s) != hipSuccess) return ARS_EDEVICE;
   const double* src = d_in;
   for (int st = 0; st < n; ++st) {
     double* dst = st + 1 == n ? d_out : (st % 2 == 0 ? d_a : d_b);

@@ -40,12 +40,11 @@ hipError_t launch_rate_reduce(const Params& P, const double* U, RateMax* slot, h
   return hipGetLastError();
 }
 
-// mode 0: clear the rate maxima; mode 1: all but the first; mode 2: clear
-// the fault latch.  A kernel, not a memset, so the call can sit inside a
-// captured graph.
+// mode 0: clear the rate maxima; mode 2: clear the fault latch.  A kernel, not
+// a memset, so the call can sit inside a captured graph.
 __global__ void __launch_bounds__(RATE_WORDS) k_ctl_prep(Control* ctl, int mode) {
-  if (mode == 0 || mode == 1) {
-    for (int i = mode; i < 3; ++i) ctl->lammax[i].w[threadIdx.x] = 0ull;
+  if (mode == 0) {
+    for (int i = 0; i < 3; ++i) ctl->lammax[i].w[threadIdx.x] = 0ull;
   }
   if (mode == 2 && threadIdx.x == 0) {
     ctl->fault = 0u;
@@ -58,13 +57,17 @@ hipError_t launch_ctl_prep(Control* ctl, int mode, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void k_dt_finish(double cfl, const Control* ctl, int slot, double* d_dt) {
-  const double r = rate_of(&ctl->lammax[slot]);
+// The next step's dt, and the rate maxima back to zero: every call leaves them
+// so for the next one, which then needs no kernel of its own in front of its
+// first step (1.5 us of a one-step call's 12).
+__global__ void __launch_bounds__(RATE_WORDS) k_dt_finish(double cfl, Control* ctl, int slot, double* d_dt) {
+  const double r = rate_of(&ctl->lammax[slot]);  // one wave: read before it clears
   if (threadIdx.x == 0) *d_dt = cfl / r;
+  for (int i = 0; i < 3; ++i) ctl->lammax[i].w[threadIdx.x] = 0ull;
 }
 
 hipError_t launch_dt_finish(const Params& P, Control* ctl, int slot, double* d_dt, hipStream_t s) {
-  hipLaunchKernelGGL(k_dt_finish, dim3(1), dim3(64), 0, s, P.cfl, ctl, slot, d_dt);
+  hipLaunchKernelGGL(k_dt_finish, dim3(1), dim3(RATE_WORDS), 0, s, P.cfl, ctl, slot, d_dt);
   return hipGetLastError();
 }
 
