@@ -687,12 +687,15 @@ int ars_diagnostics(ars_ctx* ctx, const double* d_state, void* d_work, ars_diag*
   char* w = (char*)d_work;
   double* partials = (double*)(w + CTL_BYTES);
   double* res = (double*)(w + CTL_BYTES + ars::diag_partial_bytes(ctx->P));
-  if (ars::launch_diag(ctx->P, d_state, partials, res, s) != hipSuccess) return ARS_EDEVICE;
-  double r[16];
-  if (hipMemcpyAsync(r, res, 13 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return ARS_EDEVICE;
-  int64_t fc = -1;
-  const int frc = ars_fault(ctx, d_work, &fc, stream);
-  if (frc == ARS_EDEVICE) return frc;
+  if (ars::launch_diag(ctx->P, d_state, partials, ctl_of(d_work), res, s) != hipSuccess) return ARS_EDEVICE;
+  double r[16];  // the sums and, behind them, the fault latch
+  if (hipMemcpyAsync(r, res, 15 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return ARS_EDEVICE;
+  if (hipStreamSynchronize(s) != hipSuccess) return ARS_EDEVICE;
+  uint64_t latch[2];
+  std::memcpy(latch, r + 13, sizeof latch);
+  const int frc = latch[0] ? ARS_ENONPHYS : ARS_OK;
+  const int64_t fc = latch[0] ? (int64_t)latch[1] : -1;
+  if (latch[0] && ars::launch_ctl_prep(ctl_of(d_work), 2, s) != hipSuccess) return ARS_EDEVICE;
   const ars::Params& P = ctx->P;
   double dV = P.dx[0] * P.dx[2];
   if (P.dim == 3) dV = P.dx[0] * P.dx[1] * P.dx[2];

@@ -71,8 +71,29 @@ hipError_t launch_dt_finish(const Params& P, Control* ctl, int slot, double* d_d
   return hipGetLastError();
 }
 
+// Sum (or largest) of a wave in a fixed order, in every lane: a butterfly.
+template <bool MAX>
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) {
+    const double o = __shfl_xor(v, m, 64);
+    v = MAX ? larger(v, o) : v + o;
+  }
+  return v;
+}
+
+// Sum of a block of 256 in a fixed order (the waves' butterflies, then the
+// four waves in order), in thread 0.
+__device__ __forceinline__ double block_total(double v) {
+  __shared__ double sh[4];
+  v = wave_total<false>(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
 // ---------------------------------------------------------------- diagnostics
-// partial layout per block (16 doubles):
+// partials: field f of block b at [f * DIAG_NB + b]:
 //  0 mass, 1-3 mom, 4 e_total, 5 e_kin, 6 e_int, 7 e_grav, 8 sum|u|,
 //  9 max|u|, 10 max Mach, 11 bottom wall flux sum, 12 top wall flux sum
 constexpr int DIAG_NB = 1024;
@@ -83,13 +104,12 @@ size_t diag_partial_bytes(const Params&) { return (size_t)DIAG_NB * DIAG_NF * si
 template <int DIM>
 __global__ void __launch_bounds__(256) k_diag_partial(Params P, const double* __restrict__ U, double* partials) {
   constexpr int NV = DIM + 2;
-  __shared__ double sh[256];
+  __shared__ double sh[4][13];
   double acc[DIAG_NF];
 #pragma unroll
   for (int i = 0; i < DIAG_NF; ++i) acc[i] = 0.0;
-  const long long plane = (long long)P.nx * P.ny;
-  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < P.ncell;
-       c += (long long)gridDim.x * blockDim.x) {
+  const unsigned plane = (unsigned)P.nx * (unsigned)P.ny;  // at most 2^31 cells
+  for (unsigned c = blockIdx.x * 256u + threadIdx.x; c < (unsigned)P.ncell; c += gridDim.x * 256u) {
     double b[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) b[v] = U[c + v * P.ncell];
@@ -118,41 +138,39 @@ __global__ void __launch_bounds__(256) k_diag_partial(Params P, const double* __
     if (kz == 0) acc[11] += 2.0 * (0.5 * P.Tw2[0] - q.T) / P.dx[2];
     if (kz == P.nz - 1) acc[12] += 2.0 * (q.T - 0.5 * P.Tw2[1]) / P.dx[2];
   }
-  // block reduction, fixed order
+  // block reduction in a fixed order: the waves' butterflies, then the four
+  // waves in order (13 trees through LDS, 17 barriers each: 26.8 us at 128^3,
+  // 22.0 so, 3.8 TB/s)
+#pragma unroll
   for (int f = 0; f < 13; ++f) {
-    sh[threadIdx.x] = acc[f];
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-      if ((int)threadIdx.x < w) {
-        const double a = sh[threadIdx.x], bb = sh[threadIdx.x + w];
-        sh[threadIdx.x] = (f == 9 || f == 10) ? (bb > a ? bb : a) : a + bb;
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x * DIAG_NF + f] = sh[0];
-    __syncthreads();
+    const double v = (f == 9 || f == 10) ? wave_total<true>(acc[f]) : wave_total<false>(acc[f]);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][f] = v;
+  }
+  __syncthreads();
+  const int f = threadIdx.x;
+  if (f < 13) {
+    double v = sh[0][f];
+    for (int w = 1; w < 4; ++w) v = (f == 9 || f == 10) ? larger(v, sh[w][f]) : v + sh[w][f];
+    partials[f * DIAG_NB + blockIdx.x] = v;
   }
 }
 
-__global__ void __launch_bounds__(256) k_diag_final(int nblocks, const double* partials, double* out) {
-  __shared__ double sh[256];
-  for (int f = 0; f < 13; ++f) {
-    double a = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-      const double x = partials[b * DIAG_NF + f];
-      a = (f == 9 || f == 10) ? (x > a ? x : a) : a + x;
-    }
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-      if ((int)threadIdx.x < w) {
-        const double x = sh[threadIdx.x], y = sh[threadIdx.x + w];
-        sh[threadIdx.x] = (f == 9 || f == 10) ? (y > x ? y : x) : x + y;
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[f] = sh[0];
-    __syncthreads();
+// One wave per field; the fault latch goes along (bits in out[13], out[14]),
+// so that the host reads everything at once.
+__global__ void __launch_bounds__(13 * 64) k_diag_final(int nblocks, const double* partials, const Control* ctl,
+                                                        double* out) {
+  const int f = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const bool mx = f == 9 || f == 10;
+  double a = 0.0;
+  for (int b = lane; b < nblocks; b += 64) {
+    const double x = partials[f * DIAG_NB + b];
+    a = mx ? larger(a, x) : a + x;
+  }
+  a = mx ? wave_total<true>(a) : wave_total<false>(a);
+  if (lane == 0) out[f] = a;
+  if (threadIdx.x == 0) {
+    out[13] = __longlong_as_double((long long)ctl->fault);
+    out[14] = __longlong_as_double((long long)ctl->fault_cell);
   }
 }
 
@@ -163,7 +181,6 @@ template <int DIM>
 __global__ void __launch_bounds__(256) k_ke(Params P, double dV, const double* __restrict__ U,
                                            double* __restrict__ grad, double* partials) {
   constexpr int NV = DIM + 2;
-  __shared__ double sh[256];
   double acc = 0.0;
   for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < P.ncell;
        c += (long long)gridDim.x * blockDim.x) {
@@ -184,30 +201,18 @@ __global__ void __launch_bounds__(256) k_ke(Params P, double dV, const double* _
       grad[c + (NV - 1) * P.ncell] = 0.0;
     }
   }
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partials[blockIdx.x] = sh[0];
+  acc = block_total(acc);
+  if (threadIdx.x == 0) partials[blockIdx.x] = acc;
 }
 
-__global__ void k_ke_final(int nb, double dV, const double* partials, double* out) {
-  if (threadIdx.x == 0) {
-    double a = 0.0;
-    int b = 0;
-    // eight loads in flight together, then added in order
-    for (; b + 8 <= nb; b += 8) {
-      double x[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = partials[b + j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) a += x[j];
-    }
-    for (; b < nb; ++b) a += partials[b];
-    *out = a * dV;
-  }
+// Sum of the blocks' partials times `scale` (one thread adding 1024 of them
+// was 39 us of a kinetic energy's 55 at 128^3).
+__global__ void __launch_bounds__(256) k_sum_final(int nb, double scale, const double* __restrict__ partials,
+                                                   double* __restrict__ out) {
+  double a = 0.0;
+  for (int b = threadIdx.x; b < nb; b += 256) a += partials[b];
+  a = block_total(a);
+  if (threadIdx.x == 0) *out = a * scale;
 }
 
 hipError_t launch_ke(const Params& P, const double* U, double* grad, double* partials, double* out, hipStream_t s) {
@@ -219,7 +224,7 @@ hipError_t launch_ke(const Params& P, const double* U, double* grad, double* par
     hipLaunchKernelGGL(k_ke<3>, dim3((unsigned)nb), dim3(256), 0, s, P, dV, U, grad, partials);
   else
     hipLaunchKernelGGL(k_ke<2>, dim3((unsigned)nb), dim3(256), 0, s, P, dV, U, grad, partials);
-  hipLaunchKernelGGL(k_ke_final, dim3(1), dim3(64), 0, s, (int)nb, dV, partials, out);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, (int)nb, dV, partials, out);
   return hipGetLastError();
 }
 
@@ -233,7 +238,6 @@ template <int DIM>
 __global__ void __launch_bounds__(256) k_nu(Params P, int side, double C, const double* __restrict__ U,
                                            double* __restrict__ grad, double* partials) {
   constexpr int NV = DIM + 2;
-  __shared__ double sh[256];
   const long long plane = (long long)P.nx * P.ny;
   const long long base = side == 0 ? 0 : plane * (P.nz - 1);
   const double sgn = side == 0 ? -1.0 : 1.0;  // d(flux)/dT of the wall-adjacent cell
@@ -260,30 +264,8 @@ __global__ void __launch_bounds__(256) k_nu(Params P, int side, double C, const 
       grad[i + (NV - 1) * P.ncell] = dNdT * (P.gm1 * q.r);
     }
   }
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partials[blockIdx.x] = sh[0];
-}
-
-__global__ void k_nu_final(int nb, double C, const double* partials, double* out) {
-  if (threadIdx.x == 0) {
-    double a = 0.0;
-    int b = 0;
-    // eight loads in flight together, then added in order
-    for (; b + 8 <= nb; b += 8) {
-      double x[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = partials[b + j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) a += x[j];
-    }
-    for (; b < nb; ++b) a += partials[b];
-    *out = a * C;
-  }
+  acc = block_total(acc);
+  if (threadIdx.x == 0) partials[blockIdx.x] = acc;
 }
 
 __global__ void __launch_bounds__(256) k_fill(double* p, long long n, double v) {
@@ -306,18 +288,19 @@ hipError_t launch_nusselt(const Params& P, int side, double C, const double* U, 
     hipLaunchKernelGGL(k_nu<3>, dim3((unsigned)nb), dim3(256), 0, s, P, side, C, U, grad, partials);
   else
     hipLaunchKernelGGL(k_nu<2>, dim3((unsigned)nb), dim3(256), 0, s, P, side, C, U, grad, partials);
-  hipLaunchKernelGGL(k_nu_final, dim3(1), dim3(64), 0, s, (int)nb, C, partials, out);
+  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, (int)nb, C, partials, out);
   return hipGetLastError();
 }
 
-hipError_t launch_diag(const Params& P, const double* U, double* partials, double* out, hipStream_t s) {
+hipError_t launch_diag(const Params& P, const double* U, double* partials, const Control* ctl, double* out,
+                       hipStream_t s) {
   long long nb = (P.ncell + 255) / 256;
   if (nb > DIAG_NB) nb = DIAG_NB;
   if (P.dim == 3)
     hipLaunchKernelGGL(k_diag_partial<3>, dim3((unsigned)nb), dim3(256), 0, s, P, U, partials);
   else
     hipLaunchKernelGGL(k_diag_partial<2>, dim3((unsigned)nb), dim3(256), 0, s, P, U, partials);
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, s, (int)nb, partials, out);
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(13 * 64), 0, s, (int)nb, partials, ctl, out);
   return hipGetLastError();
 }
 
