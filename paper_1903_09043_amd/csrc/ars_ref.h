@@ -36,7 +36,23 @@ inline RefGrid make_grid(const Params& P) {
 }
 
 
+// Coordinates of index i of an array of nx x ny x ... cells, x fastest, all
+// indices below 2^32: 32-bit quotients (a 64-bit one is some hundred
+// instructions, and each thread of the phase kernels needs two).
+__device__ __forceinline__ void coords32(unsigned i, unsigned nx, unsigned ny, int& x, int& y, int& z) {
+  const unsigned r = i / nx;
+  x = (int)(i - r * nx);
+  const unsigned q = r / ny;
+  y = (int)(r - q * ny);
+  z = (int)q;
+}
+
 __device__ __forceinline__ void decode(const RefGrid& G, long long i, int& qx, int& qy, int& qz) {
+  if (G.npad <= 0xffffffffll) {
+    coords32((unsigned)i, (unsigned)G.Px, (unsigned)G.Py, qx, qy, qz);
+    return;
+  }
+  // thin grids of near 2^31 cells: the padding takes the index past 32 bits
   qx = (int)(i % G.Px);
   long long r = i / G.Px;
   qy = (int)(r % G.Py);

@@ -259,10 +259,8 @@ __global__ void k_ref_update(Params P, RefGrid G, const double* __restrict__ d_d
   const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= P.ncell) return;
   constexpr int NV = DIM + 2;
-  const int x = (int)(c % P.nx);
-  const long long r = c / P.nx;
-  const int y = (int)(r % P.ny);
-  const int z = (int)(r / P.ny);
+  int x, y, z;  // at most 2^31 cells
+  coords32((unsigned)c, (unsigned)P.nx, (unsigned)P.ny, x, y, z);
   const long long i = G.pad(x + 2, DIM == 3 ? y + 2 : 0, z + 2);
   const long long n = G.npad;
   const double dt = *d_dt;
