@@ -319,7 +319,8 @@ int ars_step_ref(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, voi
  * 3D problems with periodic lateral sides of at least 5 cells and walls at
  * both vertical ends (or periodic ends with g = 0), conservative energy
  * form, run three fused tile marches whose workspace is 17 doubles per cell;
- * every other configuration runs the reference path below. */
+ * 2D problems of that kind run one kernel over tiles; every other
+ * configuration runs the reference path below. */
 size_t ars_workspace_bytes_adjoint(const ars_ctx* ctx);
 int ars_step_adjoint(ars_ctx* ctx, const double* d_state_n, const double* d_lam_np1, double* d_lam_n,
                      const double* d_dt, double* d_param_grad, void* d_work_adj, void* stream);
@@ -328,7 +329,7 @@ int ars_step_adjoint(ars_ctx* ctx, const double* d_state_n, const double* d_lam_
  * over padded arrays (forward phases recomputed, then the reverse of each
  * phase as a gather), every configuration, with a workspace of
  * ars_workspace_bytes_adjoint_ref bytes; same arguments and contract as
- * ars_step_adjoint.  Kept to check the fused marches. */
+ * ars_step_adjoint.  Kept to check the fused kernels. */
 size_t ars_workspace_bytes_adjoint_ref(const ars_ctx* ctx);
 int ars_step_adjoint_ref(ars_ctx* ctx, const double* d_state_n, const double* d_lam_np1, double* d_lam_n,
                          const double* d_dt, double* d_param_grad, void* d_work_adj, void* stream);

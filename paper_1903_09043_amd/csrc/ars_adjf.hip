@@ -1,8 +1,9 @@
 // ars_adjf.hip -- fused reverse (adjoint) of one explicit step at a frozen
-// time step, for 3D problems with periodic lateral sides and walls (or, with
+// time step, for problems with periodic lateral sides and walls (or, with
 // g = 0, periodic ends) along the vertical axis:
 //   lam^n = (dU^{n+1}/dU^n)^T lam^{n+1},  <lam^{n+1}, dU^{n+1}/d(mu, kappa)>.
 //
+// 3D (2D: one kernel over tiles, at the end of this file).
 // Three tile marches along the vertical axis replace the phase kernels of
 // ars_adjoint.hip (which stay as the reference path and serve every other
 // configuration):
@@ -1259,6 +1260,406 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_b(Params P, AdjIOF io) {
 }
 
 // ------------------------------------------------------------------------
+// 2D: the whole reverse step in one kernel
+// ------------------------------------------------------------------------
+// The phase kernels take six launches over some 60 fields in memory, each one
+// wave per SIMD at the usual sizes and a chain of loads and arithmetic of its
+// own.  Here one workgroup takes a tile of 12 x 12 cells with the 2-cell halo
+// that the reverse of a cell reaches, one thread per position, and goes
+// through the phases of A, V and B in LDS with a barrier between them: no
+// fields in memory, one launch.  Every face is reversed by the thread of its
+// lower cell, which publishes what it owes the others; 36 doubles a position
+// (73.7 KB: two workgroups per CU), the later fields over the earlier ones.
+// A tile's latency bounds it up to 512 tiles, the arithmetic of the halo
+// (16^2 / 12^2) above.  us a call, phase kernels against this (the second is
+// the caller's launch rate up to 256 x 128): 64 x 32: 38, 14; 256 x 128: 46,
+// 15; 512 x 256: 67, 19; 1024 x 512: 206, 53; 2048 x 1024: 725, 175.
+constexpr int A2_E = 16, A2_T = A2_E - 4;
+enum {
+  L2_Q = 0,    // ux, uz, T, rc, 1/rc, 1/c, p, rho
+  L2_NB = 8,   // nbar
+  L2_F = 12,   // own +x / +z faces: us, pi (x), us, pi, S (z)
+  L2_BT = 17,  // b~
+  L2_CB = 21,  // adjoints of L, A_mx, A_mz, A_E, S-bar
+  L2_M = 26,   // viscous messages: +x face (u0, u2, T right; rows d u0/dz, d u2/dz), +z face (same, d/dx)
+  L2_TOTAL = 36,
+  L2_R = L2_NB,  // right-cell adjoints of the faces (x: u, p, rc, 1/rc, 1/c; z: rho, u, p, rc, 1/rc, 1/c)
+  L2_G = 0       // wall ghosts' primitive adjoints (7: rho, u0, u2, T, and p, rc, 1/rc, 1/c: 8)
+};
+
+bool adj2_supported(const Params& P) {
+  if (P.dim != 2 || P.nc || P.bcx[0] != BC_PERIODIC || P.nx < 5) return false;
+  const bool walls = P.bcz[0] == BC_WALL && P.bcz[1] == BC_WALL;
+  const bool per = P.bcz[0] == BC_PERIODIC && P.g == 0.0 && P.nz >= 5;
+  return walls || per;
+}
+
+static long long adj2_tiles(const Params& P) {
+  return (long long)((P.nx + A2_T - 1) / A2_T) * ((P.nz + A2_T - 1) / A2_T);
+}
+
+__device__ __forceinline__ Prim<3> widen(const Prim<2>& q) {
+  Prim<3> w;
+  w.rho = q.rho; w.r = q.r; w.p = q.p; w.c = q.c; w.rc = q.rc; w.T = q.T; w.ic = q.ic; w.irc = q.irc;
+  w.u[0] = q.u[0]; w.u[1] = 0.0; w.u[2] = q.u[1];
+  return w;
+}
+
+template <bool LM, bool DISS>
+__global__ void __launch_bounds__(A2_E* A2_E, 2) k_adj2(Params P, AdjIOF io) {
+  constexpr int NPOS = A2_E * A2_E;
+  __shared__ double sm[L2_TOTAL * NPOS];
+  const int tid = threadIdx.x, px = tid % A2_E, pz = tid / A2_E;
+  const int xp = px + 1 < A2_E ? tid + 1 : tid, xm = px > 0 ? tid - 1 : tid;
+  const int dzp = pz + 1 < A2_E ? A2_E : 0, dzm = pz > 0 ? A2_E : 0;
+  const int zp = tid + dzp, zm = tid - dzm;
+  auto at = [&](int f, int pos) __attribute__((always_inline)) -> double& { return sm[f * NPOS + pos]; };
+  const int ntx = (P.nx + A2_T - 1) / A2_T;
+  const unsigned G = gridDim.x;
+  const int tile = xcd_share(blockIdx.x, (int)G);
+  const int tz = tile / ntx, tx = tile - tz * ntx;
+  const int gx = tx * A2_T + px - 2, gz = tz * A2_T + pz - 2;
+  const int cx = resolve_lat(gx, P.nx, P.bcx);
+  const bool wlo = P.bcz[0] == BC_WALL, whi = P.bcz[1] == BC_WALL;
+  int cz = gz, ghost = -1;
+  if (gz < 0 || gz >= P.nz) {
+    ghost = wlo ? (gz < 0 ? 0 : 1) : -1;
+    cz = wlo ? (gz < 0 ? 0 : P.nz - 1) : resolve_lat(gz, P.nz, P.bcz);
+  }
+  const long long N = P.ncell;
+  const long long cell = cx + (long long)P.nx * cz;
+  const bool out = px >= 2 && px < A2_E - 2 && gx < P.nx && pz >= 2 && pz < A2_E - 2 && gz < P.nz;
+  const double dt = *io.dt;
+  const double lx = dt / P.dx[0], lz = dt / P.dx[2];
+  const double phi = phi_at(P, gz);
+
+  // ---- primitives and nbar -------------------------------------------------
+  double U[4], l1[4], nb[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    U[v] = io.U[cell + v * N];
+    l1[v] = io.lam1[cell + v * N];
+  }
+  const Prim<2> qi = cons_to_prim<2>(P, U);  // of the cell, or of the cell a ghost is built from
+  Prim<2> q = qi;
+  if (ghost >= 0) q = wall_ghost<2>(P, qi, ghost, ghost == 0 ? phi_at(P, -1) - phi_at(P, 0)
+                                                             : phi_at(P, P.nz) - phi_at(P, P.nz - 1));
+#pragma unroll
+  for (int v = 0; v < 4; ++v) nb[v] = ghost >= 0 ? 0.0 : (v == 0 ? l1[0] - phi * l1[3] : l1[v]);
+  at(L2_Q + 0, tid) = q.u[0];
+  at(L2_Q + 1, tid) = q.u[1];
+  at(L2_Q + 2, tid) = q.T;
+  at(L2_Q + 3, tid) = q.rc;
+  at(L2_Q + 4, tid) = q.irc;
+  at(L2_Q + 5, tid) = q.ic;
+  at(L2_Q + 6, tid) = q.p;
+  at(L2_Q + 7, tid) = q.rho;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) at(L2_NB + v, tid) = nb[v];
+  __syncthreads();
+
+  // ---- acoustic faces ------------------------------------------------------
+  const bool wall = (gz == -1 && wlo) || (gz == P.nz - 1 && whi);  // own +z face
+  const double dphi = phi_at(P, gz + 1) - phi;
+  double usx, pix, Px, usz, piz, Pz, Sz;
+  face_lat<LM>(P, q.rc, q.irc, q.ic, q.p, q.u[0], at(L2_Q + 3, xp), at(L2_Q + 4, xp), at(L2_Q + 5, xp),
+               at(L2_Q + 6, xp), at(L2_Q + 0, xp), usx, pix, Px);
+  {
+    Prim<2> R;
+    R.rc = at(L2_Q + 3, zp); R.irc = at(L2_Q + 4, zp); R.ic = at(L2_Q + 5, zp); R.p = at(L2_Q + 6, zp);
+    R.rho = at(L2_Q + 7, zp); R.u[1] = at(L2_Q + 1, zp);
+    face_vert<LM, 2>(P, q, R, dphi, wall, usz, piz, Pz, Sz);
+  }
+  at(L2_F + 0, tid) = usx;
+  at(L2_F + 1, tid) = pix;
+  at(L2_F + 2, tid) = usz;
+  at(L2_F + 3, tid) = piz;
+  at(L2_F + 4, tid) = Sz;
+  __syncthreads();
+
+  // ---- acoustic cell values ------------------------------------------------
+  const double usxm = at(L2_F + 0, xm), uszm = at(L2_F + 2, zm);
+  double L, bt[4];
+  {
+    const double pixm = at(L2_F + 1, xm), pizm = at(L2_F + 3, zm);
+    const double Pxm = pixm * usxm, Pzm = pizm * uszm;
+    const double sb = 0.5 * (Sz + at(L2_F + 4, zm));
+    L = 1.0 + lx * (usx - usxm);
+    L = L + lz * (usz - uszm);
+    const double Amx = lx * (pix - pixm);
+    double dpz = piz - pizm;
+    dpz = dpz - sb;
+    const double Amz = lz * dpz;
+    double AE = lx * (Px - Pxm);
+    AE = AE + lz * (Pz - Pzm);
+    const double calE = U[3] + U[0] * phi;
+    const double iL = rcp_nr(L);
+    bt[0] = U[0] * iL;
+    bt[1] = (U[1] - Amx) * iL;
+    bt[2] = (U[2] - Amz) * iL;
+    bt[3] = (calE - AE) * iL;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) at(L2_BT + v, tid) = bt[v];
+  __syncthreads();
+
+  // ---- transport reverse of the own faces, then the cell values' -----------
+  double fb[4];  // (u*, Pi*) adjoints of the own +x, +z faces
+  double btb[4], Gx[4], Gz[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    btb[v] = 0.0;
+    Gx[v] = lx * (at(L2_NB + v, xp) - nb[v]);
+    Gz[v] = lz * (at(L2_NB + v, zp) - nb[v]);
+  }
+  // the -x, -z faces, whose upwind cell this one is where u* < 0
+  if (!(usxm >= 0.0)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) btb[v] += (lx * (nb[v] - at(L2_NB + v, xm))) * usxm;
+  }
+  if (!((gz == 0 && wlo) || (gz == P.nz && whi)) && !(uszm >= 0.0)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) btb[v] += (lz * (nb[v] - at(L2_NB + v, zm))) * uszm;
+  }
+  auto transport = [&](const double* Gb, double us, double pi, int nbp, int dn, double& usb, double& pib)
+      __attribute__((always_inline)) {
+    const bool upL = us >= 0.0;
+    usb = 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double bn = at(L2_BT + v, nbp);
+      const double bu = upL ? bt[v] : bn;
+      usb += Gb[v] * (v == 3 ? bu + pi : bu);
+    }
+    pib = Gb[1 + dn] + Gb[3] * us;
+    if (upL) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) btb[v] += Gb[v] * us;
+    }
+  };
+  transport(Gx, usx, pix, xp, 0, fb[0], fb[1]);
+  if (wall) {
+    fb[2] = 0.0;
+    fb[3] = Gz[2];
+  } else {
+    transport(Gz, usz, piz, zp, 1, fb[2], fb[3]);
+  }
+  double consb[4], cb[5];  // adjoints of L, A_mx, A_mz, A_E, S-bar
+  {
+    const double iL = rcp_nr(L);
+    double Lb = 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      consb[v] = btb[v] * iL;
+      Lb += btb[v] * bt[v];
+    }
+    cb[0] = -Lb * iL;
+    cb[1] = -consb[1];
+    cb[2] = -consb[2];
+    cb[3] = -consb[3];
+    cb[4] = -lz * cb[2] + lz * nb[2];  // A_mz = lam_z ([Pi*] - S-bar); the update adds lam_z S-bar
+    consb[0] += phi * consb[3];        // calE = E + rho Phi
+    if (ghost >= 0) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) cb[i] = 0.0;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 5; ++i) at(L2_CB + i, tid) = cb[i];
+
+  // ---- viscous and heat-flux reverse of the own faces ----------------------
+  double vb[3] = {0.0, 0.0, 0.0};  // adjoints of u0, u2, T
+  double mu_acc = 0.0, ka_acc = 0.0;
+  if (DISS) {
+    const double u0 = q.u[0], u2 = q.u[1];
+    const double qx = P.qidx[0], qz = P.qidx[2];
+    double M[10];
+#pragma unroll
+    for (int i = 0; i < 10; ++i) M[i] = 0.0;
+    auto face = [&](int dn, const double* Gb4, double* m) __attribute__((always_inline)) {
+      // t: the tangential axis' neighbours of the own and of the other cell
+      const int R = dn == 0 ? xp : zp;
+      const int tp = dn == 0 ? zp : xp, tm = dn == 0 ? zm : xm;
+      const int Rtp = dn == 0 ? xp + dzp : (px + 1 < A2_E ? zp + 1 : zp);
+      const int Rtm = dn == 0 ? xp - dzm : (px > 0 ? zp - 1 : zp);
+      const double uL[3] = {u0, 0.0, u2}, uR[3] = {at(L2_Q + 0, R), 0.0, at(L2_Q + 1, R)};
+      const double TR = at(L2_Q + 2, R);
+      double g[3][3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[a][k] = 0.0;
+      const double idn = P.idx[dn];
+      g[dn][0] = (uR[0] - uL[0]) * idn;
+      g[dn][2] = (uR[2] - uL[2]) * idn;
+      const int ta = 2 - dn;  // tangential axis
+      const double qt = dn == 0 ? qz : qx;
+      g[ta][0] = ((at(L2_Q + 0, tp) - at(L2_Q + 0, tm)) + (at(L2_Q + 0, Rtp) - at(L2_Q + 0, Rtm))) * qt;
+      g[ta][2] = ((at(L2_Q + 1, tp) - at(L2_Q + 1, tm)) + (at(L2_Q + 1, Rtp) - at(L2_Q + 1, Rtm))) * qt;
+      const double Gb[5] = {Gb4[0], Gb4[1], 0.0, Gb4[2], Gb4[3]};
+      double uLb[3], uRb[3], TLb, TRb, gb[3][3], mub, kab;
+      visc_adj(P, dn, idn, g, uL, uR, q.T, TR, Gb, uLb, uRb, TLb, TRb, gb, mub, kab);
+      vb[0] += uLb[0];
+      vb[1] += uLb[2];
+      vb[2] += TLb;
+      m[0] = uRb[0];
+      m[1] = uRb[2];
+      m[2] = TRb;
+      m[3] = gb[ta][0];
+      m[4] = gb[ta][2];
+      const bool own = out || (dn == 2 && gz == -1 && wlo && tz == 0 && px >= 2 && px < A2_E - 2 && gx < P.nx);
+      if (own) {
+        mu_acc += mub;
+        ka_acc += kab;
+      }
+    };
+    if (ghost < 0) face(0, Gx, M);                      // +x faces of the cells
+    if (ghost < 0 || gz == -1) face(2, Gz, M + 5);      // +z faces between cells and at both walls
+#pragma unroll
+    for (int i = 0; i < 10; ++i) at(L2_M + i, tid) = M[i];
+  }
+  __syncthreads();
+
+  // ---- face-solver reverse of the own faces --------------------------------
+  double pb[9];  // rho, u0, -, u2, p, rc, 1/rc, 1/c, T (as prim_adj takes them)
+#pragma unroll
+  for (int i = 0; i < 9; ++i) pb[i] = 0.0;
+  {
+    double bl[6], br[6];
+    const double usb = fb[0] + lx * (cb[0] - at(L2_CB + 0, xp));
+    const double pib = fb[1] + lx * (cb[1] - at(L2_CB + 1, xp));
+    const double Pb = lx * (cb[3] - at(L2_CB + 3, xp));
+    face_adj<LM>(P, false, false, 0.0, usx, pix, 0.0, q.u[0], q.p, q.rc, q.irc, q.ic, at(L2_Q + 0, xp),
+                 at(L2_Q + 6, xp), at(L2_Q + 3, xp), at(L2_Q + 4, xp), at(L2_Q + 5, xp), usb, pib, Pb, 0.0, bl, br);
+    pb[1] += bl[1];
+    pb[4] += bl[2];
+    pb[5] += bl[3];
+    pb[6] += bl[4];
+    pb[7] += bl[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) at(L2_R + i, tid) = br[1 + i];
+  }
+  {
+    double bl[6], br[6];
+    const double usb = fb[2] + lz * (cb[0] - at(L2_CB + 0, zp));
+    const double pib = fb[3] + lz * (cb[2] - at(L2_CB + 2, zp));
+    const double Pb = lz * (cb[3] - at(L2_CB + 3, zp));
+    const double Sb = 0.5 * cb[4] + 0.5 * at(L2_CB + 4, zp);
+    face_adj<LM>(P, true, wall, dphi, usz, piz, Sz, q.u[1], q.p, q.rc, q.irc, q.ic, at(L2_Q + 1, zp),
+                 at(L2_Q + 6, zp), at(L2_Q + 3, zp), at(L2_Q + 4, zp), at(L2_Q + 5, zp), usb, pib, Pb, Sb, bl, br);
+    pb[0] += bl[0];
+    pb[3] += bl[1];
+    pb[4] += bl[2];
+    pb[5] += bl[3];
+    pb[6] += bl[4];
+    pb[7] += bl[5];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) at(L2_R + 5 + i, tid) = br[i];
+  }
+  __syncthreads();
+
+  // ---- gather --------------------------------------------------------------
+  // A wall ghost has no lateral face of its own and, outside its wall, no
+  // vertical one: of the faces above only its wall face counts.
+  if (ghost >= 0) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) pb[i] = 0.0;
+  }
+  if (ghost == 0) {  // lower cell of the bottom wall face: its share again, from the face alone
+    double bl[6], br[6];
+    const double pib = fb[3] + lz * (cb[2] - at(L2_CB + 2, zp));
+    const double Pb = lz * (cb[3] - at(L2_CB + 3, zp));
+    const double usb = lz * (cb[0] - at(L2_CB + 0, zp));
+    const double Sb = 0.5 * cb[4] + 0.5 * at(L2_CB + 4, zp);
+    face_adj<LM>(P, true, wall, dphi, usz, piz, Sz, q.u[1], q.p, q.rc, q.irc, q.ic, at(L2_Q + 1, zp),
+                 at(L2_Q + 6, zp), at(L2_Q + 3, zp), at(L2_Q + 4, zp), at(L2_Q + 5, zp), usb, pib, Pb, Sb, bl, br);
+    pb[0] = bl[0];
+    pb[3] = bl[1];
+    pb[4] = bl[2];
+    pb[5] = bl[3];
+    pb[6] = bl[4];
+    pb[7] = bl[5];
+  } else {
+    if (ghost < 0) {
+      pb[1] += at(L2_R + 0, xm);
+      pb[4] += at(L2_R + 1, xm);
+      pb[5] += at(L2_R + 2, xm);
+      pb[6] += at(L2_R + 3, xm);
+      pb[7] += at(L2_R + 4, xm);
+    }
+    pb[0] += at(L2_R + 5, zm);
+    pb[3] += at(L2_R + 6, zm);
+    pb[4] += at(L2_R + 7, zm);
+    pb[5] += at(L2_R + 8, zm);
+    pb[6] += at(L2_R + 9, zm);
+    pb[7] += at(L2_R + 10, zm);
+  }
+  if (DISS) {
+    const double qx = P.qidx[0], qz = P.qidx[2];
+    const int xmzm = xm - dzm, xmzp = xm + dzp, xpzm = xp - dzm;
+    // right-cell shares of the -x and -z faces
+    vb[0] += at(L2_M + 0, xm) + at(L2_M + 5, zm);
+    vb[1] += at(L2_M + 1, xm) + at(L2_M + 6, zm);
+    vb[2] += at(L2_M + 2, xm) + at(L2_M + 7, zm);
+    // tangential rows: of the x faces above and below, of the z faces beside
+    vb[0] += qz * ((at(L2_M + 3, zm) - at(L2_M + 3, zp)) + (at(L2_M + 3, xmzm) - at(L2_M + 3, xmzp)));
+    vb[1] += qz * ((at(L2_M + 4, zm) - at(L2_M + 4, zp)) + (at(L2_M + 4, xmzm) - at(L2_M + 4, xmzp)));
+    vb[0] += qx * ((at(L2_M + 8, xm) - at(L2_M + 8, xp)) + (at(L2_M + 8, xmzm) - at(L2_M + 8, xpzm)));
+    vb[1] += qx * ((at(L2_M + 9, xm) - at(L2_M + 9, xp)) + (at(L2_M + 9, xmzm) - at(L2_M + 9, xpzm)));
+    pb[1] += vb[0];
+    pb[3] += vb[1];
+    pb[8] += vb[2];
+  }
+  // wall ghosts hand their primitive adjoints to the cell they are built from
+  const bool next_to_wall = (gz == 0 && wlo) || (gz == P.nz - 1 && whi);
+  constexpr int GF[8] = {0, 1, 3, 4, 5, 6, 7, 8};
+  __syncthreads();
+  if (gz == -1 || gz == P.nz) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) at(L2_G + i, tid) = pb[GF[i]];
+  }
+  __syncthreads();
+  if (next_to_wall) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      if (side == 0 ? !(gz == 0 && wlo) : !(gz == P.nz - 1 && whi)) continue;
+      double gb[9];
+      gb[2] = 0.0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) gb[GF[i]] = at(L2_G + i, side == 0 ? zm : zp);
+      const double d = side == 0 ? phi_at(P, -1) - phi_at(P, 0) : phi_at(P, P.nz) - phi_at(P, P.nz - 1);
+      const Prim<2> gq = wall_ghost<2>(P, q, side, d);
+      ghost_adj(P, side, d, widen(q), widen(gq), gb, pb);
+    }
+  }
+  if (out) {
+    const double m[3] = {U[1], 0.0, U[2]};
+    double Ub[5];
+    prim_adj(P, widen(q), m, pb, Ub);
+    io.lam0[cell] = l1[0] + (consb[0] + Ub[0]);
+    io.lam0[cell + N] = l1[1] + (consb[1] + Ub[1]);
+    io.lam0[cell + 2 * N] = l1[2] + (consb[2] + Ub[3]);
+    io.lam0[cell + 3 * N] = l1[3] + (consb[3] + Ub[4]);
+  }
+
+  // ---- mu / kappa partials of the tile, in a fixed order --------------------
+  if (DISS) {
+    __shared__ double red[2][NPOS / 64];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      mu_acc += __shfl_xor(mu_acc, off, 64);
+      ka_acc += __shfl_xor(ka_acc, off, 64);
+    }
+    if ((tid & 63) == 0) {
+      red[0][tid >> 6] = mu_acc;
+      red[1][tid >> 6] = ka_acc;
+    }
+    __syncthreads();
+    if (tid < 2) io.partial[2 * tile + tid] = ((red[tid][0] + red[tid][1]) + red[tid][2]) + red[tid][3];
+  }
+}
+
+// ------------------------------------------------------------------------
 // Host side
 // ------------------------------------------------------------------------
 template <bool LM, bool DISS>
@@ -1306,6 +1707,29 @@ hipError_t launch_step_adjoint_fused(const Params& P, const double* Un, const do
   if (lm) return adjf_t<true, false>(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
   if (ds) return adjf_t<false, true>(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
   return adjf_t<false, false>(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
+}
+
+hipError_t launch_step_adjoint_2d(const Params& P, const double* Un, const double* lam_np1, double* lam_n,
+                                  const double* d_dt, double* d_param_grad, void* wadj, hipStream_t s) {
+  AdjIOF io{};
+  io.U = Un;
+  io.lam1 = lam_np1;
+  io.lam0 = lam_n;
+  io.partial = (double*)wadj;
+  io.dt = d_dt;
+  const dim3 grid((unsigned)adj2_tiles(P)), block(A2_E * A2_E);
+  const bool lm = P.low_mach != 0;
+  if (lm && P.diss)
+    hipLaunchKernelGGL((k_adj2<true, true>), grid, block, 0, s, P, io);
+  else if (lm)
+    hipLaunchKernelGGL((k_adj2<true, false>), grid, block, 0, s, P, io);
+  else if (P.diss)
+    hipLaunchKernelGGL((k_adj2<false, true>), grid, block, 0, s, P, io);
+  else
+    hipLaunchKernelGGL((k_adj2<false, false>), grid, block, 0, s, P, io);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !P.diss || !d_param_grad) return e;
+  return launch_adj_params_final((int)adj2_tiles(P), io.partial, d_param_grad, s);
 }
 
 }  // namespace ars

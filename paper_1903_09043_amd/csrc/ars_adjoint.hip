@@ -865,12 +865,19 @@ hipError_t launch_step_adjoint_ref(const Params& P, const double* Un, const doub
 }
 
 size_t adjoint_workspace_bytes(const Params& P) {
+  // (the 2D tiles need two doubles each: less than the phase kernels' fields)
   return adjf_supported(P) ? adjf_workspace_bytes(P) : adjoint_ref_workspace_bytes(P);
 }
 
 hipError_t launch_step_adjoint(const Params& P, const double* Un, const double* lam_np1, double* lam_n,
                                const double* d_dt, double* d_param_grad, void* wadj, hipStream_t s) {
   if (adjf_supported(P)) return launch_step_adjoint_fused(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
+  // (measured at that kernel) tiles write lam^n while others still read their
+  // halos: only where it shares no memory with the inputs
+  const size_t len = (size_t)P.ncell * 4;
+  auto apart = [&](const double* in) { return lam_n + len <= in || in + len <= lam_n; };
+  if (adj2_supported(P) && apart(Un) && apart(lam_np1))
+    return launch_step_adjoint_2d(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
   return launch_step_adjoint_ref(P, Un, lam_np1, lam_n, d_dt, d_param_grad, wadj, s);
 }
 
