@@ -35,6 +35,7 @@
 // and the host reads the residual norm every few iterations.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -635,8 +636,9 @@ static_assert((CT_X * CT_Z) % BS == 0 && CT_X % 64 == 0, "tile rows are whole wa
 // of (p', q'), (r', q'), (q', q') and the exact (r', r').  Iteration 0 takes
 // alpha = beta = 0 (r' = r, p' = r).  Four sums per block in the layout
 // part[k * pstride + block].
+template <int NT>
 __device__ __forceinline__ void block_sum4(double (&v)[4]) {
-  __shared__ double sh4[4][BS / 64];
+  __shared__ double sh4[4][NT / 64];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
 #pragma unroll
@@ -651,12 +653,31 @@ __device__ __forceinline__ void block_sum4(double (&v)[4]) {
   for (int k = 0; k < 4; ++k) {
     double t = sh4[k][0];
 #pragma unroll
-    for (int w = 1; w < BS / 64; ++w) t = t + sh4[k][w];
+    for (int w = 1; w < NT / 64; ++w) t = t + sh4[k][w];
     v[k] = t;
   }
 }
 
 enum { CGS_PQ = 0, CGS_RQ, CGS_QQ, CGS_RR };
+
+// alpha and beta of an iteration from the previous one's block sums.
+template <int NT>
+__device__ __forceinline__ void cg_scalars(const double* __restrict__ pprev, int pstride, double& alpha,
+                                           double& beta) {
+  double v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    double a = 0.0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += NT) a = a + pprev[k * pstride + i];
+    v[k] = a;
+  }
+  block_sum4<NT>(v);
+  const double rr = v[CGS_RR];
+  alpha = v[CGS_PQ] != 0.0 ? rr / v[CGS_PQ] : 0.0;
+  const double rrn = (rr - 2.0 * alpha * v[CGS_RQ]) + (alpha * alpha) * v[CGS_QQ];
+  beta = rr != 0.0 ? rrn / rr : 0.0;
+  __syncthreads();
+}
 
 __global__ __launch_bounds__(BS) void k_cg_iter_2d(Params P, const double* __restrict__ d_dt,
                                                    const double* __restrict__ rin, const double* __restrict__ qin,
@@ -673,21 +694,7 @@ __global__ __launch_bounds__(BS) void k_cg_iter_2d(Params P, const double* __res
   __shared__ int colm[CP_X];
   __shared__ int rowm[CP_Z];
   double alpha = 0.0, beta = 0.0;
-  if (it > 0) {
-    double v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      double a = 0.0;
-      for (int i = threadIdx.x; i < (int)gridDim.x; i += BS) a = a + pprev[k * pstride + i];
-      v[k] = a;
-    }
-    block_sum4(v);
-    const double rr = v[CGS_RR];
-    alpha = v[CGS_PQ] != 0.0 ? rr / v[CGS_PQ] : 0.0;
-    const double rrn = (rr - 2.0 * alpha * v[CGS_RQ]) + (alpha * alpha) * v[CGS_QQ];
-    beta = rr != 0.0 ? rrn / rr : 0.0;
-    __syncthreads();
-  }
+  if (it > 0) cg_scalars<BS>(pprev, pstride, alpha, beta);
   const double dt = *d_dt;
   const double lx = dt / P.dx[0], lz = dt / P.dx[2], hK = P.hK;
   const int nx = P.nx, nz = P.nz;
@@ -775,14 +782,182 @@ __global__ __launch_bounds__(BS) void k_cg_iter_2d(Params P, const double* __res
     }
     __syncthreads();  // the next tile overwrites the LDS
   }
-  block_sum4(acc);
+  block_sum4<BS>(acc);
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) pcur[k * pstride + blockIdx.x] = acc[k];
   }
 }
 
-// (r, r) of the last fused 2D iteration, for the host's convergence test.
+// The same iteration in 3D: a unit is a 32 x 16 column of cells over zc planes,
+// one thread a column.  A column's own values of five planes stay in
+// registers; a plane's p, tau and 1/(rho c) go to LDS for the lateral
+// neighbours, with the halo (2 for p, 1 for the others, no corners) read by
+// 192 of the 512 threads; two LDS planes in turn, one barrier a plane, the
+// next plane's loads in flight meanwhile.  Memory bounds it: 11 values a cell
+// are read or written, and some 4 more for the halo (loads two planes ahead
+// change nothing).  Against k_cg_apply and k_cg_xr, which read 41 and 4 values
+// a cell in two launches, us an iteration: 32^3 14, 13; 96^3 38, 30; 128^3
+// 69, 47; 200^3 342, 221.
+constexpr int C3_X = 32, C3_Y = 16, C3_T = C3_X * C3_Y;
+constexpr int C3_PX = C3_X + 4, C3_PY = C3_Y + 4;
+
+__device__ __forceinline__ int image_of(int v, int n, bool wall) {
+  if (wall) return v < 0 ? 0 : (v < n ? v : n - 1);
+  const int g = v % n;
+  return g < 0 ? g + n : g;
+}
+
+__global__ __launch_bounds__(C3_T) void k_cg_iter_3d(Params P, const double* __restrict__ d_dt,
+                                                     const double* __restrict__ rin, const double* __restrict__ qin,
+                                                     const double* __restrict__ pin, double* __restrict__ rout,
+                                                     double* __restrict__ qout, double* __restrict__ pout,
+                                                     double* __restrict__ x, const double* __restrict__ tau,
+                                                     const double* __restrict__ irc, const double* __restrict__ irc2,
+                                                     const double* __restrict__ pprev, double* __restrict__ pcur,
+                                                     int pstride, int it, int wallmask, int zc) {
+  __shared__ double sP[2][C3_PY * C3_PX];
+  __shared__ double sT[2][C3_PY * C3_PX];
+  __shared__ double sI[2][C3_PY * C3_PX];
+  double alpha = 0.0, beta = 0.0;
+  if (it > 0) cg_scalars<C3_T>(pprev, pstride, alpha, beta);
+  const double dt = *d_dt, hK = P.hK;
+  const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
+  const int nx = P.nx, ny = P.ny, nz = P.nz, nxy = nx * ny;
+  const bool wx = wallmask & 1, wy = (wallmask >> 1) & 1, wz = (wallmask >> 2) & 1;
+  const int ntx = (nx + C3_X - 1) / C3_X, nty = (ny + C3_Y - 1) / C3_Y, nch = (nz + zc - 1) / zc;
+  const long long units = (long long)ntx * nty * nch;
+  const unsigned G = gridDim.x, b = blockIdx.x;
+  const unsigned lw = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  const long long u0 = units * lw / G, u1 = units * (lw + 1) / G;
+  const int tid = threadIdx.x, tx = tid % C3_X, ty = tid / C3_X;
+  const int pos = (ty + 2) * C3_PX + tx + 2;
+  // halo position of this thread: rows -2, -1, C3_Y, C3_Y + 1, then columns;
+  // tau and 1/(rho c) at the inner ones
+  int hx = tx, hy = ty;
+  bool inner = false;
+  const bool halo = tid < 4 * (C3_X + C3_Y);
+  if (tid < 4 * C3_X) {
+    const int k = tid / C3_X;
+    hy = k < 2 ? k - 2 : C3_Y + k - 2;
+    inner = k == 1 || k == 2;
+  } else if (halo) {
+    const int h = tid - 4 * C3_X, k = h / C3_Y;
+    hy = h % C3_Y;
+    hx = k < 2 ? k - 2 : C3_X + k - 2;
+    inner = k == 1 || k == 2;
+  }
+  const int hpos = (hy + 2) * C3_PX + hx + 2;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  int s = 0;
+  for (long long u = u0; u < u1; ++u) {
+    const int tile = (int)(u / nch), z0 = (int)(u - (long long)tile * nch) * zc, z1 = min(z0 + zc, nz);
+    const int x0 = (tile % ntx) * C3_X, y0 = (tile / ntx) * C3_Y;
+    const int gx = x0 + tx, gy = y0 + ty;
+    const bool in = gx < nx && gy < ny;
+    const int col = image_of(gx, nx, wx) + nx * image_of(gy, ny, wy);
+    const int hcol = image_of(x0 + hx, nx, wx) + nx * image_of(y0 + hy, ny, wy);
+    // loads of step v: r, q, p (and x) of plane v, tau and 1/(rho c) of v - 1,
+    // the halo and 1/(rho c^2) of v - 2
+    double nr, nq, np, nX = 0.0, nt = 0.0, ni = 0.0, nc = 0.0, hr = 0.0, hq = 0.0, hp = 0.0, ht = 0.0, hi = 0.0;
+    auto load = [&](int v) __attribute__((always_inline)) {
+      const int i = image_of(v, nz, wz) * nxy + col;
+      nr = rin[i];
+      nq = qin[i];
+      np = pin[i];
+      if (v >= z0 && v < z1) nX = x[i];
+      if (v >= z0) {
+        const int j = image_of(v - 1, nz, wz) * nxy + col;
+        nt = tau[j];
+        ni = irc[j];
+      }
+      if (v >= z0 + 2) {
+        const int z = (v - 2) * nxy;
+        nc = irc2[z + col];
+        if (halo) {
+          hr = rin[z + hcol];
+          hq = qin[z + hcol];
+          hp = pin[z + hcol];
+          if (inner) {
+            ht = tau[z + hcol];
+            hi = irc[z + hcol];
+          }
+        }
+      }
+    };
+    load(z0 - 2);
+    double p0 = 0, p1 = 0, p2 = 0, p3 = 0, p4 = 0;  // p of planes v - 4 .. v
+    double r2 = 0, r3 = 0, r4 = 0;                  // r of planes v - 2 .. v
+    double t1 = 0, t2 = 0, t3 = 0, i1 = 0, i2 = 0, i3 = 0;  // of planes v - 3 .. v - 1
+    for (int v = z0 - 2; v <= z1 + 1; ++v) {
+      const double pold = np, xo = nX, ic2 = nc;
+      p0 = p1; p1 = p2; p2 = p3; p3 = p4;
+      r2 = r3; r3 = r4;
+      t1 = t2; t2 = t3; i1 = i2; i2 = i3;
+      t3 = nt; i3 = ni;
+      r4 = nr - alpha * nq;
+      p4 = r4 + beta * pold;
+      const int z = v - 2;
+      if (z >= z0) {
+        sP[s][pos] = p2;
+        sT[s][pos] = t2;
+        sI[s][pos] = i2;
+        if (halo) {
+          sP[s][hpos] = (hr - alpha * hq) + beta * hp;
+          if (inner) {
+            sT[s][hpos] = ht;
+            sI[s][hpos] = hi;
+          }
+        }
+      }
+      if (v <= z1) load(v + 1);
+      if (v >= z0 && v < z1 && in) {
+        const int i = v * nxy + col;
+        rout[i] = r4;
+        pout[i] = p4;
+        x[i] = xo + alpha * pold;
+        acc[CGS_RR] = acc[CGS_RR] + r4 * r4;
+      }
+      if (z < z0) continue;
+      __syncthreads();
+      // velocities of the cells c - e, c, c + e of an axis, then u* of the two
+      // faces (0 on a wall face)
+      auto axis = [&](double lam, double Pm2, double Pm1, double Pp1, double Pp2, double tm, double tp, double im,
+                      double ip, bool first, bool last) __attribute__((always_inline)) {
+        const double um = -(lam * tm) * (0.5 * (p2 - Pm2));
+        const double uc = -(lam * t2) * (0.5 * (Pp1 - Pm1));
+        const double up = -(lam * tp) * (0.5 * (Pp2 - p2));
+        double usm = 0.5 * (um + uc) - (p2 - Pm1) * (hK * dmin2(im, i2));
+        double usp = 0.5 * (uc + up) - (Pp1 - p2) * (hK * dmin2(i2, ip));
+        if (first) usm = 0.0;
+        if (last) usp = 0.0;
+        return lam * (usp - usm);
+      };
+      double div = 0.0;
+      div = div + axis(lx, sP[s][pos - 2], sP[s][pos - 1], sP[s][pos + 1], sP[s][pos + 2], sT[s][pos - 1],
+                       sT[s][pos + 1], sI[s][pos - 1], sI[s][pos + 1], wx && gx == 0, wx && gx == nx - 1);
+      div = div + axis(ly, sP[s][pos - 2 * C3_PX], sP[s][pos - C3_PX], sP[s][pos + C3_PX], sP[s][pos + 2 * C3_PX],
+                       sT[s][pos - C3_PX], sT[s][pos + C3_PX], sI[s][pos - C3_PX], sI[s][pos + C3_PX],
+                       wy && gy == 0, wy && gy == ny - 1);
+      div = div + axis(lz, p0, p1, p3, p4, t1, t3, i1, i3, wz && z == 0, wz && z == nz - 1);
+      if (in) {
+        const double y = p2 * ic2 + div;
+        qout[z * nxy + col] = y;
+        acc[CGS_PQ] = acc[CGS_PQ] + p2 * y;
+        acc[CGS_RQ] = acc[CGS_RQ] + r2 * y;
+        acc[CGS_QQ] = acc[CGS_QQ] + y * y;
+      }
+      s ^= 1;
+    }
+  }
+  block_sum4<C3_T>(acc);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) pcur[k * pstride + blockIdx.x] = acc[k];
+  }
+}
+
+// (r, r) of the last fused iteration, for the host's convergence test.
 __global__ __launch_bounds__(BS) void k_cg_check_rr(const double* __restrict__ rr_parts, int nb,
                                                     double* __restrict__ sc) {
   const double rr = sum_parts(rr_parts, nb);
@@ -934,12 +1109,7 @@ struct Imex {
     // per axis all the same)
     const int wallmask = (P.bcx[0] == BC_WALL ? 1 : 0) | (DIM == 3 && P.bcy[0] == BC_WALL ? 2 : 0) |
                          (P.bcz[0] == BC_WALL ? 4 : 0);
-    const unsigned gb = nb < (unsigned)CG_BLOCKS ? nb : (unsigned)CG_BLOCKS;  // k_cg_xr
-    unsigned ga = gb;                                                          // the product
-    if (DIM == 2) {
-      const long long tiles = (long long)((P.nx + CT_X - 1) / CT_X) * ((P.nz + CT_Z - 1) / CT_Z);
-      ga = tiles < CG_BLOCKS ? (unsigned)tiles : (unsigned)CG_BLOCKS;
-    }
+    const unsigned gb = nb < (unsigned)CG_BLOCKS ? nb : (unsigned)CG_BLOCKS;
     hipLaunchKernelGGL(k_fill0, dim3(nb), dim3(BS), 0, s, L.n, L.t);
     if (apply(L.t, L.b, 1) != hipSuccess) return ARS_EDEVICE;
     hipLaunchKernelGGL(k_neg, dim3(nb), dim3(BS), 0, s, L.n, L.b);
@@ -964,11 +1134,7 @@ struct Imex {
     }
     TrigCoef tc;
     if (prefer_trig(h, std::sqrt(rr0 / target), max_iter, &tc)) return iterate_trig(target, max_iter, its, tc, gb, wallmask);
-    if constexpr (DIM == 2) {
-      return iterate_2d(target, max_iter, its, ga, wallmask);
-    } else {
-      return iterate_3d(target, max_iter, its, ga, gb, wallmask);
-    }
+    return iterate_cg(target, max_iter, its, wallmask);
   }
 
   // Scratch of the trigonometric preconditioner: the reference workspace from
@@ -988,7 +1154,7 @@ struct Imex {
   // taken, and half a block of CG_CHECK iterations for the late read of the
   // residual.  Time per iteration as measured (with the host's
   // reads): without, 12.9 us at 64^2, 13.2 at 512^2, 27.8 at 1024^2 in 2D and
-  // 14 us at 32^3, 38 at 96^3; with, 68 us at 64^2 (the transforms' launches,
+  // 13 us at 32^3, 30 at 96^3, 221 at 200^3; with, 68 us at 64^2 (the transforms' launches,
   // product, updates and a read of the residual), 390 at 1024^2.
   bool prefer_trig(const double* h, double red, int max_iter, TrigCoef* tc) const {
     const double n = (double)L.n;
@@ -1022,7 +1188,7 @@ struct Imex {
       const double len = a == 0 ? P.nx : (a == 1 ? P.ny : P.nz);
       t_with += 2.0 * std::fmax(6.0, 2.0 * n * len / TRIG_RATE + n * 16.0 / MEM);
     }
-    const double t_without = DIM == 2 ? std::fmax(12.5, 3.0 + n * 24e-6) : std::fmax(14.0, 6.0 + n * 36e-6);
+    const double t_without = DIM == 2 ? std::fmax(12.5, 3.0 + n * 24e-6) : std::fmax(11.5, 9.0 + n * 23e-6);
     return 20.0 + with * t_with < without * t_without;
   }
 
@@ -1057,71 +1223,60 @@ struct Imex {
     return ARS_ENOCONV;
   }
 
-  // 3D: two kernels an iteration (k_cg_apply, k_cg_xr).
-  int iterate_3d(double target, int max_iter, int* its, unsigned ga, unsigned gb, int wallmask) {
-    double* const part_pq = L.part;
-    double* const part_rr = L.part + (CG_BLOCKS > DOT_BLOCKS ? CG_BLOCKS : DOT_BLOCKS);
-    double* pv[2] = {L.p, L.b};  // p = 0 on entry, so the first p is r
-    int it = 0;
-    for (; it < max_iter; ++it) {
-      double* po = pv[it & 1];
-      double* pn = pv[(it + 1) & 1];
-      hipLaunchKernelGGL(k_cg_apply<3>, dim3(ga), dim3(BS), 0, s, P, d_dt, L.r, po, pn, L.rh, L.sv, L.t, L.v,
-                         part_rr, (int)gb, part_pq, L.sc, it, wallmask);
-      hipLaunchKernelGGL(k_cg_xr, dim3(gb), dim3(BS), 0, s, L.n, pn, L.v, L.x, L.r, part_pq, (int)ga, part_rr, L.sc,
-                         it);
-      if (it % CG_CHECK == CG_CHECK - 1 || it + 1 == max_iter) {
-        hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(BS), 0, s, part_rr, (int)gb, L.sc);
-        double rr = 0.0;
-        if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
-        if (!std::isfinite(rr)) return ARS_ENOCONV;
-        if (rr <= target) {
-          ++it;
-          break;
-        }
-      }
-    }
-    if (its) *its = it;
-    if (it >= max_iter) {
-      double rr = 0.0;
-      if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
-      if (!(rr <= target)) return ARS_ENOCONV;
-    }
-    return hipGetLastError() == hipSuccess ? ARS_OK : ARS_EDEVICE;
-  }
-
-  // 2D: one kernel an iteration (k_cg_iter_2d).  Iteration i reads the
+  // One kernel an iteration (k_cg_iter_2d, k_cg_iter_3d).  Iteration i reads the
   // residual, product and direction of set (i + 1) & 1 and writes set i & 1
   // (set 1 starts as r0, 0, 0: k_bicg_start zeroed p and v), and its four
   // block sums go to sum set i & 1.
-  int iterate_2d(double target, int max_iter, int* its, unsigned ga, int wallmask) {
+  int iterate_cg(double target, int max_iter, int* its, int wallmask) {
+    unsigned ga = 1;
+    int zc = 1;
+    if (DIM == 2) {
+      const long long tiles = (long long)((P.nx + CT_X - 1) / CT_X) * ((P.nz + CT_Z - 1) / CT_Z);
+      ga = tiles < CG_BLOCKS ? (unsigned)tiles : (unsigned)CG_BLOCKS;
+    } else {
+      // planes a unit: the fewest for the busiest CU, a unit costing 1.5 more
+      // for its halo planes; at most two workgroups are resident per CU
+      const long long tiles = (long long)((P.nx + C3_X - 1) / C3_X) * ((P.ny + C3_Y - 1) / C3_Y);
+      double best = 1e300;
+      for (int ch = 1; ch <= P.nz && (ch == 1 || tiles * ch <= 512); ++ch) {
+        const int c = (P.nz + ch - 1) / ch;
+        const long long units = tiles * ((P.nz + c - 1) / c);
+        const double cost = (double)((units + 255) / 256) * (c + 1.5);
+        if (cost < best) {
+          best = cost;
+          zc = c;
+          ga = (unsigned)std::min(512LL, units);
+        }
+      }
+    }
     const int ps = CG_BLOCKS > DOT_BLOCKS ? CG_BLOCKS : DOT_BLOCKS;
     double* R[2] = {L.r2, L.r};
     double* Q[2] = {L.q2, L.v};
     double* Pv[2] = {L.b, L.p};
     double* S[2] = {L.part, L.part + 4 * ps};
-    int it = 0;
-    for (; it < max_iter; ++it) {
-      const int o = it & 1, in = o ^ 1;
-      hipLaunchKernelGGL(k_cg_iter_2d, dim3(ga), dim3(BS), 0, s, P, d_dt, R[in], Q[in], Pv[in], R[o], Q[o], Pv[o],
-                         L.x, L.rh, L.sv, L.t, S[in], S[o], ps, L.sc, it, wallmask);
-      if (it % CG_CHECK == CG_CHECK - 1 || it + 1 == max_iter) {
+    // kernel i applies the update of iteration i - 1 and starts its own; the
+    // 2D count is of kernels, the 3D count of updates
+    const int lead = DIM == 3 ? 1 : 0;
+    int it = 0;  // iterations counted
+    double rr = 0.0;
+    for (int k = 0; it < max_iter; ++k) {
+      const int o = k & 1, in = o ^ 1;
+      if (DIM == 2)
+        hipLaunchKernelGGL(k_cg_iter_2d, dim3(ga), dim3(BS), 0, s, P, d_dt, R[in], Q[in], Pv[in], R[o], Q[o], Pv[o],
+                           L.x, L.rh, L.sv, L.t, S[in], S[o], ps, L.sc, k, wallmask);
+      else
+        hipLaunchKernelGGL(k_cg_iter_3d, dim3(ga), dim3(C3_T), 0, s, P, d_dt, R[in], Q[in], Pv[in], R[o], Q[o],
+                           Pv[o], L.x, L.rh, L.sv, L.t, S[in], S[o], ps, k, wallmask, zc);
+      it = k + 1 - lead;
+      if (it > 0 && (it % CG_CHECK == 0 || it == max_iter)) {
         hipLaunchKernelGGL(k_cg_check_rr, dim3(1), dim3(BS), 0, s, S[o] + CGS_RR * ps, (int)ga, L.sc);
-        double rr = 0.0;
         if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
         if (!std::isfinite(rr)) return ARS_ENOCONV;
-        if (rr <= target) {
-          ++it;
-          break;
-        }
+        if (rr <= target) break;
       }
     }
     if (its) *its = it;
-    if (it >= max_iter) {
-      double rr = 0.0;
-      if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
-      if (!(rr <= target)) return ARS_ENOCONV;
-    }
+    if (!(rr <= target)) return ARS_ENOCONV;
     return hipGetLastError() == hipSuccess ? ARS_OK : ARS_EDEVICE;
   }
 
