@@ -26,7 +26,9 @@
 // Krylov solver on the N unknowns Pi: conjugate gradients when every axis is
 // periodic or walled at both ends (the operator is then symmetric positive
 // definite), plain or preconditioned by the constant-coefficient operator's
-// inverse (ars_trig.hip), BiCGSTAB otherwise (outflow).  The operator is applied
+// inverse (ars_trig.hip), BiCGSTAB otherwise (outflow).  With conjugate
+// gradients the system is formed and the step finished by the passes of
+// ars_imex_phase.hip.  For BiCGSTAB the operator is applied
 // matrix-free: one kernel extends Pi to the ghost cells, one forms the
 // velocities of every padded cell from the Pi* of its two faces per axis
 // (ghosts by the boundary rules), one forms every row from the u* of the
@@ -41,6 +43,7 @@
 
 #include "../../include/ars.h"
 #include "ars_dev.h"
+#include "ars_imex_phase.h"
 #include "ars_internal.h"
 #include "ars_ref.h"
 #include "ars_trig.h"
@@ -428,68 +431,6 @@ __global__ void k_bicg_scalars(double* __restrict__ sc) {
 // sits between kernels).  A last-block-arrives reduction would need
 // device-scope fences (one per block, an L2 write-back each on a part whose
 // XCDs have L2s of their own), which cost far more.
-
-// Smallest (sign = 1) or largest (-1) v of a block, in every thread.
-__device__ __forceinline__ double block_extreme(double v, double sign) {
-  __shared__ double sh[BS / 64];
-  v = v * -sign;
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  for (int w = 0; w < BS / 64; ++w) v = larger(v, sh[w]);
-  return v * -sign;
-}
-
-// Coefficients of the homogeneous operator per interior cell: tau, 1/(rho c)
-// and 1/(rho c^2) (the rows' scale), out of the padded workspace, and each
-// block's smallest and largest of the three into part (six rows of gridDim).
-template <int DIM>
-__global__ __launch_bounds__(BS) void k_cg_coef(Params P, RefGrid G, const double* __restrict__ W,
-                                                double* __restrict__ tau, double* __restrict__ irc,
-                                                double* __restrict__ irc2, double* __restrict__ part) {
-  const long long n = G.npad;
-  const double inf = __builtin_huge_val();
-  double lo[3] = {inf, inf, inf}, hi[3] = {0.0, 0.0, 0.0};
-  for (unsigned c = blockIdx.x * BS + threadIdx.x; c < (unsigned)P.ncell; c += gridDim.x * BS) {
-    int cx, cy, cz;
-    coords32(c, (unsigned)P.nx, (unsigned)P.ny, cx, cy, cz);
-    const long long q = G.pad(cx + 2, DIM == 3 ? cy + 2 : 0, cz + 2);
-    const double v[3] = {1.0 / (W[R_RC * n + q] * W[R_C * n + q]), W[R_R * n + q], W[R_IRC * n + q]};
-    irc2[c] = v[0];
-    tau[c] = v[1];
-    irc[c] = v[2];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = v[k] < lo[k] ? v[k] : lo[k];
-      hi[k] = v[k] > hi[k] ? v[k] : hi[k];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const double a = block_extreme(lo[k], 1.0), b = block_extreme(hi[k], -1.0);
-    if (threadIdx.x == 0) {
-      part[(2 * k) * gridDim.x + blockIdx.x] = a;
-      part[(2 * k + 1) * gridDim.x + blockIdx.x] = b;
-    }
-  }
-}
-
-// The coefficients' ranges over the blocks, and the time step, for the host.
-__global__ __launch_bounds__(BS) void k_cg_range(const double* __restrict__ part, int nb, const double* __restrict__ d_dt,
-                                                 double* __restrict__ sc) {
-  for (int k = 0; k < 6; ++k) {
-    const double sign = k % 2 == 0 ? 1.0 : -1.0;
-    double v = part[k * nb];
-    for (int i = threadIdx.x; i < nb; i += BS) {
-      const double o = part[k * nb + i];
-      v = sign * o < sign * v ? o : v;
-    }
-    v = block_extreme(v, sign);
-    if (threadIdx.x == 0) sc[SC_RANGE + k] = v;
-  }
-  if (threadIdx.x == 0) sc[SC_DT] = *d_dt;
-}
 
 // Index offsets of the neighbours k - 2, k - 1, k + 1, k + 2 of coordinate
 // k on an axis of m >= 2 cells and stride st: periodic images, or on a
@@ -1099,10 +1040,11 @@ struct Imex {
     return hipGetLastError() == hipSuccess ? ARS_OK : ARS_EDEVICE;
   }
 
-  // Conjugate gradients on the same system (every axis periodic or walled).  The
-  // BiCGSTAB-only vectors hold the coefficients (rh: tau, sv: 1/(rho c),
-  // t: 1/(rho c^2)) and b, once the first residual is formed, the second p.
-  int solve_cg(double tol, int max_iter, int* its) {
+  // Conjugate gradients on the same system of the state U (every axis periodic
+  // or walled; imex_begin forms it).  The BiCGSTAB-only vectors hold the
+  // coefficients (rh: tau, sv: 1/(rho c), t: 1/(rho c^2)) and, in b, the
+  // second p.
+  int solve_cg(const double* U, double tol, int max_iter, int* its) {
     const unsigned nb = nblk(L.n);
     // bit a: the physical axis a is walled at both ends (a configuration
     // admits walls on the vertical axis only; the products take the mask
@@ -1110,18 +1052,9 @@ struct Imex {
     const int wallmask = (P.bcx[0] == BC_WALL ? 1 : 0) | (DIM == 3 && P.bcy[0] == BC_WALL ? 2 : 0) |
                          (P.bcz[0] == BC_WALL ? 4 : 0);
     const unsigned gb = nb < (unsigned)CG_BLOCKS ? nb : (unsigned)CG_BLOCKS;
-    hipLaunchKernelGGL(k_fill0, dim3(nb), dim3(BS), 0, s, L.n, L.t);
-    if (apply(L.t, L.b, 1) != hipSuccess) return ARS_EDEVICE;
-    hipLaunchKernelGGL(k_neg, dim3(nb), dim3(BS), 0, s, L.n, L.b);
-    hipLaunchKernelGGL(k_imex_x0<DIM>, dim3(nblk(P.ncell)), dim3(BS), 0, s, P, L.G, L.W, L.x);
-    if (apply(L.x, L.r, 0) != hipSuccess) return ARS_EDEVICE;
-    // r = b - A x0 (also clears p and v, and copies r to rh, overwritten next)
-    hipLaunchKernelGGL(k_bicg_start, dim3(nb), dim3(BS), 0, s, L.n, L.b, L.r, L.rh, L.p, L.v, L.sc);
-    dot(L.b, L.b, SC_BB);
-    dot(L.r, L.r, SC_CG_RR);  // (r, r) of iteration 0
-    const unsigned nc = nb < (unsigned)CG_BLOCKS ? nb : (unsigned)CG_BLOCKS;
-    hipLaunchKernelGGL(k_cg_coef<DIM>, dim3(nc), dim3(BS), 0, s, P, L.G, L.W, L.rh, L.sv, L.t, L.part);
-    hipLaunchKernelGGL(k_cg_range, dim3(1), dim3(BS), 0, s, L.part, (int)nc, d_dt, L.sc);
+    static_assert(SC_CG_RR == SC_BB + 1 && SC_DT == SC_RANGE + 6 && IMEX_BEGIN_BLOCKS <= CG_BLOCKS, "imex_begin");
+    const ImexSystem S{L.x, L.r, L.p, L.v, L.rh, L.sv, L.t, L.part, L.sc + SC_BB, L.sc + SC_RANGE};
+    if (imex_begin(P, U, L.W, L.ext, d_dt, S, s) != hipSuccess) return ARS_EDEVICE;
     double h[SC_N];
     if (hipMemcpyAsync(h, L.sc, SC_N * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess) return ARS_EDEVICE;
     if (hipStreamSynchronize(s) != hipSuccess) return ARS_EDEVICE;
@@ -1225,7 +1158,7 @@ struct Imex {
 
   // One kernel an iteration (k_cg_iter_2d, k_cg_iter_3d).  Iteration i reads the
   // residual, product and direction of set (i + 1) & 1 and writes set i & 1
-  // (set 1 starts as r0, 0, 0: k_bicg_start zeroed p and v), and its four
+  // (set 1 starts as r0, 0, 0: imex_begin zeroed p and v), and its four
   // block sums go to sum set i & 1.
   int iterate_cg(double target, int max_iter, int* its, int wallmask) {
     unsigned ga = 1;
@@ -1316,28 +1249,34 @@ static int imex_steps(const Params& P, double* d_state, double* d_tmp, Control* 
   int total = 0;
   double* src = d_state;
   double* dst = d_tmp;
+  // conjugate gradients, and the step in place, where the operator is
+  // symmetric: every axis periodic or walled at both ends
+  auto sym = [](const int* bc) {
+    return (bc[0] == BC_PERIODIC && bc[1] == BC_PERIODIC) || (bc[0] == BC_WALL && bc[1] == BC_WALL);
+  };
+  const bool symmetric = sym(P.bcx) && sym(P.bcz) && (DIM == 2 || sym(P.bcy)) && P.nx >= 2 && P.nz >= 2 &&
+                         (DIM == 2 || P.ny >= 2) && P.ncell < (1LL << 31) - (long long)BS;
   for (int st = 0; st < nsteps; ++st) {
     M.d_dt = d_dt_sched + st;
-    if (launch_ref_forward(P, src, M.L.W, M.d_dt, s) != hipSuccess) return ARS_EDEVICE;
-    int its = 0;
-    // conjugate gradients where the operator is symmetric: every axis
-    // periodic or walled at both ends
-    auto sym = [](const int* bc) {
-      return (bc[0] == BC_PERIODIC && bc[1] == BC_PERIODIC) || (bc[0] == BC_WALL && bc[1] == BC_WALL);
-    };
-    const bool symmetric = sym(P.bcx) && sym(P.bcz) && (DIM == 2 || sym(P.bcy)) && P.nx >= 2 && P.nz >= 2 &&
-                           (DIM == 2 || P.ny >= 2) && P.ncell < (1LL << 31) - (long long)BS;
-    const int rc = symmetric ? M.solve_cg(tol, max_iter, &its) : M.solve(tol, max_iter, &its);
+    int its = 0, rc;
+    if (symmetric) {
+      rc = M.solve_cg(d_state, tol, max_iter, &its);
+    } else {
+      if (launch_ref_forward(P, src, M.L.W, M.d_dt, s) != hipSuccess) return ARS_EDEVICE;
+      rc = M.solve(tol, max_iter, &its);
+    }
     total += its;
     if (rc != ARS_OK) {
       if (h_iters) *h_iters = total;
       return rc;
     }
-    if (M.finish(dst, ctl) != hipSuccess) return ARS_EDEVICE;
+    if (symmetric) {
+      if (imex_finish(P, d_state, M.L.W, M.L.ext, M.L.x, M.d_dt, ctl, s) != hipSuccess) return ARS_EDEVICE;
+    } else {
+      if (M.finish(dst, ctl) != hipSuccess) return ARS_EDEVICE;
+      std::swap(src, dst);
+    }
     if (d_t) hipLaunchKernelGGL(k_add_t, dim3(1), dim3(64), 0, s, d_t, M.d_dt);
-    double* w = src;
-    src = dst;
-    dst = w;
   }
   if (src != d_state &&
       hipMemcpyAsync(d_state, src, (size_t)(P.dim + 2) * P.ncell * sizeof(double), hipMemcpyDeviceToDevice, s) !=
