@@ -1088,7 +1088,8 @@ struct Imex {
   // residual.  Time per iteration as measured (with the host's
   // reads): without, 12.9 us at 64^2, 13.2 at 512^2, 27.8 at 1024^2 in 2D and
   // 13 us at 32^3, 30 at 96^3, 221 at 200^3; with, 68 us at 64^2 (the transforms' launches,
-  // product, updates and a read of the residual), 390 at 1024^2.
+  // product, updates and a read of the residual), 390 at 1024^2 (330 since the
+  // transforms are half products: near the line the plain iteration is taken).
   bool prefer_trig(const double* h, double red, int max_iter, TrigCoef* tc) const {
     const double n = (double)L.n;
     if (P.nx > TRIG_MAXN || P.ny > TRIG_MAXN || P.nz > TRIG_MAXN || (long long)P.ny * P.nz > (1 << 21) ||
