@@ -30,6 +30,8 @@
 // barrier and a walk of the whole plane's annulus per shell (w 3.0, rows 6.7,
 // columns 10.8, shells 11.8 us); 15.7 now (rows 5.7, columns 7.2, sum 3.4: each
 // a chain of barriers at one workgroup per CU).
+#include <algorithm>
+
 #include "ars_dev.h"
 #include "ars_internal.h"
 
@@ -77,18 +79,31 @@ __global__ void __launch_bounds__(256) k_spec_w(Params P, const double* __restri
 // (kx group of 64, row tile of 16, component c), wave w the 16 x 16 tile of
 // rows y0.. and wave numbers k0 = 64 bx + 16 w ..; real and imaginary
 // parts in two accumulators; X_c[y][k], k <= n_x / 2.  Out-of-range rows,
-// columns and K entries contribute zeros.
+// columns and K entries contribute zeros.  STATE: the block forms its rows of w
+// from the state in LDS, behind the twiddles; W then is the density's plane.
+template <bool STATE>
 __global__ void __launch_bounds__(256) k_spec_rows(Params P, const double* __restrict__ W, double* __restrict__ Xr,
                                                    double* __restrict__ Xi) {
   extern __shared__ double tw[];
   const int nx = P.nx, ny = P.ny, kn = nx / 2 + 1, c = blockIdx.z;
   fill_twiddles(tw, nx);
+  const int pitch = nx | 1;  // odd: the 16 rows of an operand read fall on different banks
+  if (STATE) {
+    const int rows = min(16, ny - (int)blockIdx.y * 16);
+    const double* rho = W + (long long)blockIdx.y * 16 * nx;
+    const double* mom = rho + (long long)(1 + c) * P.ncell;
+    for (int f = threadIdx.x; f < rows * nx; f += 256) {
+      const int r = f / nx;
+      tw[2 * nx + r * pitch + (f - r * nx)] = sqrt(rho[f]) * (mom[f] / rho[f]);
+    }
+  }
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = lane & 15, q = lane >> 4;
   const int y0 = blockIdx.y * 16, k0 = blockIdx.x * 64 + wave * 16;
   const int y = y0 + i, k = k0 + i;  // A row of this lane, B column of this lane
   const double* Wr = W + ((long long)c * ny + (y < ny ? y : 0)) * nx;
+  const double* own = tw + 2 * nx + i * pitch;
   const int dk = (int)((4LL * k) % nx);
   int e = (int)(((long long)k * q) % nx);  // k x mod n_x at x = q
   dbl4 ar = {0.0, 0.0, 0.0, 0.0}, ai = {0.0, 0.0, 0.0, 0.0};
@@ -100,7 +115,7 @@ __global__ void __launch_bounds__(256) k_spec_rows(Params P, const double* __res
     for (int j = 0; j < 8; ++j) {
       const int x = x0 + 4 * j + q;
       const bool in = x < nx;
-      a[j] = (in && y < ny) ? Wr[x] : 0.0;
+      a[j] = (in && y < ny) ? (STATE ? own[x] : Wr[x]) : 0.0;
       br[j] = (in && k < kn) ? tw[e] : 0.0;
       bi[j] = (in && k < kn) ? tw[nx + e] : 0.0;
       e += dk;
@@ -417,11 +432,20 @@ hipError_t launch_spectrum(const Params& P, const double* U, int kz, double* E, 
     hipLaunchKernelGGL(k_fft_cols, dim3(kn), dim3(256), (size_t)(2 + 2 * nc) * P.ny * sizeof(double), s, P, ly, nc,
                        Xr, Xi, part);
   } else {
-    long long nb = (N * P.dim + 255) / 256;
-    if (nb > 4096) nb = 4096;
-    hipLaunchKernelGGL(k_spec_w, dim3((unsigned)nb), dim3(256), 0, s, P, U, kz, Wp);
     const dim3 g((kn + 63) / 64, (unsigned)((P.ny + 15) / 16), (unsigned)P.dim);
-    hipLaunchKernelGGL(k_spec_rows, g, dim3(256), (size_t)2 * P.nx * sizeof(double), s, P, Wp, Xr, Xi);
+    // twiddles and 16 rows of w; where they fit (up to 455 cells), w needs no
+    // launch of its own, of which a small plane's call consists: us a call with
+    // and without one 100 x 60 24.2, 20.2; 130 x 130 29.6, 28.1; 250 x 249 41.9,
+    // 40.4 (formed by every wave of a row in registers: 24.0 at 100 x 60)
+    const size_t own = ((size_t)2 * P.nx + 16 * (size_t)(P.nx | 1)) * sizeof(double);
+    const size_t lds = (size_t)2 * P.nx * sizeof(double);
+    if (own <= FFT_LDS_DOUBLES * sizeof(double)) {
+      hipLaunchKernelGGL(k_spec_rows<true>, g, dim3(256), own, s, P, U + (long long)kz * N, Xr, Xi);
+    } else {
+      const long long nb = std::min((N * P.dim + 255) / 256, 4096LL);
+      hipLaunchKernelGGL(k_spec_w, dim3((unsigned)nb), dim3(256), 0, s, P, U, kz, Wp);
+      hipLaunchKernelGGL(k_spec_rows<false>, g, dim3(256), lds, s, P, Wp, Xr, Xi);
+    }
     hipLaunchKernelGGL(k_spec_cols, g, dim3(256), (size_t)2 * P.ny * sizeof(double), s, P, Xr, Xi, Wp);
     hipLaunchKernelGGL(k_spec_part, dim3(kn), dim3(256), (size_t)(P.ny + 2 * (P.ny / 2 + 1)) * sizeof(double), s, P, Wp,
                        part);

@@ -36,7 +36,7 @@
 // 32-bit offsets for the loads (50 us) or eight waves on the halves of a stage
 // (50 us): what is left is neither address arithmetic nor too few waves.
 // The Mach 1e-3 vortex at acoustic CFL 275, 1024^2 (one implicit step, residual
-// 1e-10): 736 plain iterations, 20.5 ms; one preconditioned iteration, 0.50 ms,
+// 1e-10): 736 plain iterations, 20.5 ms; one preconditioned iteration, 0.51 ms,
 // of which the four transforms take 0.21.
 #include <algorithm>
 
