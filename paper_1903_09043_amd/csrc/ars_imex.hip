@@ -420,12 +420,13 @@ __global__ void k_bicg_scalars(double* __restrict__ sc) {
 // operator stays symmetric.  Outflow copies make u* at the boundary face
 // the edge cell's velocity, which breaks the symmetry: BiCGSTAB there.)
 // The operator is a star stencil of radius 2 on the unknowns (neighbour
-// indices wrapped on periodic axes, clamped on walled ones).  In 3D an
-// iteration is two streaming kernels: (1) p = r + beta p_old and q = A p
-// on the fly, with the block sums of (p, q); (2) x += alpha p,
-// r -= alpha q, with those of (r, r).  In 2D it is one kernel
-// (k_cg_iter_2d, through an LDS tile): the previous iteration's x, r
-// updates are done on the fly as well.  Each kernel starts by adding the
+// indices wrapped on periodic axes, clamped on walled ones).  An
+// iteration is one kernel (k_cg_iter_2d over LDS tiles, k_cg_iter_3d over
+// columns of cells): it applies the previous iteration's update of x and r,
+// forms p and q = A p on the fly and leaves the block sums of both.  The
+// preconditioned iteration takes two streaming kernels: (1) p = z + beta p_old
+// and q = A p (k_cg_apply), (2) x += alpha p, r -= alpha q (k_cg_xr).
+// Each kernel starts by adding the
 // block sums it needs itself, every block in the same fixed order (so every
 // block forms the same alpha and beta bit for bit, and no one-block launch
 // sits between kernels).  A last-block-arrives reduction would need
