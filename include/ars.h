@@ -213,6 +213,11 @@ int ars_compute_dt(ars_ctx* ctx, const double* d_state, void* d_work, double* d_
  * next step's dt and *d_t has been advanced by the sum of the dts used.
  * d_tmp: caller scratch state of the same size.  The result is in d_state.
  * d_dt_log (nullable): receives the dt of every step (n_steps doubles).
+ * The workspace has to have been prepared once (ars_workspace_init or
+ * ars_compute_dt): every call, here and in ars_step_to, leaves its rate
+ * maxima cleared for the next one, one that ends in ARS_EDEVICE too as long
+ * as the stream still takes a launch (after a device error that outlasts the
+ * call, prepare it again).
  * Asynchronous; numerical faults are latched. */
 int ars_step(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, int n_steps, double* d_t, double* d_dt,
              double* d_dt_log, void* stream);

@@ -22,6 +22,15 @@ using ars::CTL_BYTES;
 
 int check(hipError_t e) { return e == hipSuccess ? ARS_OK : ARS_EDEVICE; }
 
+// Error end of a call that has queued CFL steps: their rates wait in the
+// maxima for the kernel that forms the next dt and clears them, which this
+// call does not reach, and the next call's steps would take the larger of
+// those and their own.
+int fail_clean(ars::Control* ctl, hipStream_t s) {
+  (void)ars::launch_ctl_prep(ctl, 0, s);
+  return ARS_EDEVICE;
+}
+
 bool lateral_ok(const ars_config* c, int a) {
   for (int s = 0; s < 2; ++s) {
     const int b = c->bc[a][s];
@@ -495,14 +504,14 @@ int ars_step(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, int n, 
     io.t = d_t;
     io.dt_log = d_dt_log ? d_dt_log + st : nullptr;
     io.ctl = ctl;
-    if (ars::launch_step_fused(ctx->P, src, dst, io, ctx->ts, s) != hipSuccess) return ARS_EDEVICE;
+    if (ars::launch_step_fused(ctx->P, src, dst, io, ctx->ts, s) != hipSuccess) return fail_clean(ctl, s);
     std::swap(src, dst);
   }
   if (src != d_state) {
     if (hipMemcpyAsync(d_state, src, ctx->len * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess)
-      return ARS_EDEVICE;
+      return fail_clean(ctl, s);
   }
-  return check(ars::launch_dt_finish(ctx->P, ctl, n % 3, d_dt, s));
+  return ars::launch_dt_finish(ctx->P, ctl, n % 3, d_dt, s) == hipSuccess ? ARS_OK : fail_clean(ctl, s);
 }
 
 int ars_step_sched(ars_ctx* ctx, double* d_state, double* d_tmp, void* d_work, int n, const double* d_dt_sched,
@@ -549,10 +558,10 @@ int ars_step_to(ars_ctx* ctx, const double* d_in, double* d_a, double* d_b, doub
     io.t = d_t;
     io.dt_log = d_dt_log ? d_dt_log + st : nullptr;
     io.ctl = ctl;
-    if (ars::launch_step_fused(ctx->P, src, dst, io, ctx->ts, s) != hipSuccess) return ARS_EDEVICE;
+    if (ars::launch_step_fused(ctx->P, src, dst, io, ctx->ts, s) != hipSuccess) return fail_clean(ctl, s);
     src = dst;
   }
-  return check(ars::launch_dt_finish(ctx->P, ctl, n % 3, d_dt, s));
+  return ars::launch_dt_finish(ctx->P, ctl, n % 3, d_dt, s) == hipSuccess ? ARS_OK : fail_clean(ctl, s);
 }
 
 int ars_step_sched_to(ars_ctx* ctx, const double* d_in, double* d_a, double* d_b, double* d_out, void* d_work,

@@ -1,0 +1,201 @@
+// Host driver for what the library's calls launch and in which order, without
+// a GPU: the HIP runtime's entry points that those calls use are defined here
+// (the library, linked dynamically, then calls these), "device" buffers are
+// host memory, and of the kernels only what they do to the control block is
+// carried out.  Any of the launches and copies of a call can be made to fail.
+// Built and run by tests/test_launch_host.py, which names the check to run.
+#include <dlfcn.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "../../include/ars.h"
+#include "../../paper_1903_09043_amd/csrc/ars_internal.h"
+
+namespace {
+
+int ops = 0;             // launches and copies of the present call
+int fail_at = -1;        // the one that fails
+hipError_t pending = hipSuccess;
+double state_rate = 1.0; // rate of every state that a step kernel writes
+unsigned last_block = 0; // threads of the last k_batch workgroup
+int num_cu = 256;
+
+hipError_t op() {
+  if (ops++ != fail_at) return hipSuccess;
+  pending = hipErrorLaunchFailure;
+  return pending;
+}
+
+double largest(const ars::RateMax* m) {
+  double v = 0.0;
+  for (unsigned long long w : m->w) {
+    double x;
+    std::memcpy(&x, &w, sizeof x);
+    v = std::max(v, x);
+  }
+  return v;
+}
+
+void fold(ars::RateMax* m, double v) {
+  unsigned long long b;
+  std::memcpy(&b, &v, sizeof b);
+  m->w[0] = std::max(m->w[0], b);
+}
+
+void clear(ars::Control* c) {
+  for (auto& m : c->lammax) std::memset(&m, 0, sizeof m);
+}
+
+}  // namespace
+
+extern "C" {
+
+hipError_t hipLaunchKernel(const void* f, dim3, dim3 block, void** a, size_t, hipStream_t) {
+  const hipError_t e = op();
+  if (e != hipSuccess) return e;
+  Dl_info info{};
+  const std::string name = dladdr(f, &info) && info.dli_sname ? info.dli_sname : "";
+  if (name.find("k_step_fused") != std::string::npos) {
+    const ars::Params& P = *(const ars::Params*)a[0];
+    const ars::StepIO& io = *(const ars::StepIO*)a[3];
+    const double dt = io.rate_in ? P.cfl / largest(io.rate_in) : *io.dt_in;
+    if (io.dt_log) *io.dt_log = dt;
+    if (io.clear_slot) std::memset(io.clear_slot, 0, sizeof *io.clear_slot);
+    if (io.rate_out) fold(io.rate_out, state_rate);
+  } else if (name.find("k_ctl_prep") != std::string::npos) {
+    if (*(int*)a[1] == 0) clear(*(ars::Control**)a[0]);
+  } else if (name.find("k_dt_finish") != std::string::npos) {
+    ars::Control* c = *(ars::Control**)a[1];
+    **(double**)a[3] = *(double*)a[0] / largest(&c->lammax[*(int*)a[2]]);
+    clear(c);
+  } else if (name.find("k_batch") != std::string::npos) {
+    last_block = block.x;
+  }
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  const hipError_t e = op();
+  if (e == hipSuccess) std::memcpy(d, s, n);
+  return e;
+}
+hipError_t hipGetLastError(void) {
+  const hipError_t e = pending;
+  pending = hipSuccess;
+  return e;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeMultiprocessorCount ? num_cu : 0;
+  return hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+  *n = 8;
+  return hipSuccess;
+}
+
+static struct { dim3 g, b; size_t m; hipStream_t s; } config;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) {
+  config = {g, b, m, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s) {
+  *g = config.g;
+  *b = config.b;
+  *m = config.m;
+  *s = config.s;
+  return hipSuccess;
+}
+
+}  // extern "C"
+
+namespace {
+
+ars_config rb2d(int nx, int nz) {
+  ars_config c{};
+  c.dim = 2;
+  c.n[0] = nx;
+  c.n[1] = nz;
+  c.n[2] = 1;
+  c.L[0] = 2.0;
+  c.L[1] = c.L[2] = 1.0;
+  c.gamma = 5.0 / 3.0;
+  c.g = 1.0;
+  c.mu = 2e-3;
+  c.kappa = 3e-3;
+  c.K = 1.1;
+  c.cfl = 0.4;
+  c.low_mach = 1;
+  c.bc[1][0] = c.bc[1][1] = ARS_BC_WALL;
+  c.wall_noslip = 1;
+  c.thermal[0] = c.thermal[1] = ARS_T_FIXED;
+  c.T_wall[0] = 1.0;
+  c.T_wall[1] = 0.5;
+  return c;
+}
+
+// A call of n CFL steps that fails at any of its launches or copies, on states
+// of rate 100, then one on states of rate 1 with the same workspace: the time
+// steps of the second are those of its own states.
+int failed_step() {
+  int bad = 0;
+  const ars_config cfg = rb2d(8, 6);
+  ars_ctx* x = nullptr;
+  if (ars_create(&cfg, &x) != ARS_OK) return 1;
+  const size_t len = ars_state_len(x);
+  std::vector<double> A(len), B(len), C(len), D(len), work(ars_workspace_bytes(x) / 8 + 1);
+  double t = 0.0, dt = 0.0, log[4];
+  for (int to = 0; to < 2; ++to) {
+    auto call = [&](int n) {
+      ops = 0;
+      const int rc = to ? ars_step_to(x, A.data(), B.data(), C.data(), D.data(), work.data(), n, &t, &dt, log, nullptr)
+                        : ars_step(x, A.data(), B.data(), work.data(), n, &t, &dt, log, nullptr);
+      pending = hipSuccess;
+      return rc;
+    };
+    for (int n = 1; n <= 4; ++n) {
+      fail_at = -1;
+      ars_workspace_init(x, work.data(), nullptr);
+      if (call(n) != ARS_OK) return 1;
+      const int total = ops;
+      for (int k = 0; k < total; ++k) {
+        ars_workspace_init(x, work.data(), nullptr);
+        state_rate = 100.0;
+        dt = cfg.cfl;
+        fail_at = k;
+        const int rc = call(n);
+        fail_at = -1;
+        state_rate = 1.0;
+        dt = cfg.cfl;
+        const int rc2 = call(4);
+        bool ok = rc == ARS_EDEVICE && rc2 == ARS_OK && dt == cfg.cfl;
+        for (double d : log) ok = ok && d == cfg.cfl;
+        if (!ok) {
+          ++bad;
+          std::printf("to %d, %d steps, operation %d of %d failed: rc %d, then %d, dts %g %g %g %g, next %g\n", to, n, k,
+                      total, rc, rc2, log[0], log[1], log[2], log[3], dt);
+        }
+      }
+    }
+  }
+  ars_destroy(x);
+  return bad;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  int bad = 1;
+  if (what == "failed_step") bad = failed_step();
+  std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
+  return bad ? 1 : 0;
+}

@@ -1,0 +1,37 @@
+"""What the library's calls launch, on the CPU: a driver in tests/host/ stands
+in for the HIP runtime and carries out what the kernels do to the control
+block, so that a launch or a copy can be made to fail in the middle of a call
+and launch shapes can be read.  No GPU is used."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_1903_09043_amd as A
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    A.lib()
+    exe = str(tmp_path_factory.mktemp("host") / "launch_driver")
+    cmd = [HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
+           os.path.join(ROOT, "tests", "host", "launch_driver.cpp"), "-x", "none", A.LIB_PATH,
+           "-Wl,-rpath," + os.path.dirname(A.LIB_PATH), "-rdynamic", "-ldl", "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+@pytest.mark.parametrize("what", ["failed_step"])
+def test_launches(driver, what):
+    """failed_step: the time steps after a call that ended in an error are
+    those of the new call's own states."""
+    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=120)
+    print(r.stdout[-4000:], r.stderr[-2000:])
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok")
