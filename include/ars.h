@@ -413,7 +413,12 @@ int64_t ars_revolve_cost(int n, int s);
  *                    built-in cost model).  Results do not depend on the
  *                    tiling.  Invalidates the captured graph; call
  *                    ars_batch_bind again afterwards.
- * ars_batch_bind     writes the table for these buffers (t = 0) and
+ * ars_batch_get_tiling  the tiling that a bind writes into the table and
+ *                    launches take: the one set, or else the one that the
+ *                    last ars_batch_bind chose for its device (before the
+ *                    first: 4 rows).
+ * ars_batch_bind     chooses the tiling unless the caller or the tuner has
+ *                    set one, writes the table for these buffers (t = 0) and
  *                    synchronises `stream`.
  * ars_batch_step     advances every instance n_steps steps, dt of each step
  *                    = cfl / (max rate of its current state).  Asynchronous.

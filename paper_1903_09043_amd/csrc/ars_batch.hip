@@ -194,7 +194,7 @@ hipError_t launch_batch(ars_batch* b, void* table, int nsteps, hipStream_t s) {
   ars::BatchInst* insts = (ars::BatchInst*)base;
   const ars::Params* params = (const ars::Params*)(base + params_offset(b->n));
   const int* order = (const int*)(base + order_offset(b->n));
-  if (b->run_rows == 8)
+  if (b->rows == 8)
     launch_rows<8>(b, insts, params, order, nsteps, s);
   else
     launch_rows<4>(b, insts, params, order, nsteps, s);
@@ -210,10 +210,10 @@ hipError_t launch_batch(ars_batch* b, void* table, int nsteps, hipStream_t s) {
 // and 256 x 128 in equal parts), a step: 213 us with 4 rows, 191 with 8; 100
 // of them: 172 and 143.  (The marches are split; whole: 221 and 200, 199 and
 // 159.)
-double batch_makespan(const ars_batch* b, int rows) {
-  constexpr int CUS = 256, WAVES = 8;
-  const int slots = CUS * (WAVES / rows);
-  const bool alone = b->n * rows <= CUS * 4;  // at most one wave per SIMD
+double batch_makespan(const ars_batch* b, int rows, int cus) {
+  constexpr int WAVES = 8;
+  const int slots = cus * (WAVES / rows);
+  const bool alone = (long long)b->n * rows <= 4ll * cus;  // at most one wave per SIMD
   std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
   double last = 0.0;
   for (int k : b->order) {
@@ -230,18 +230,26 @@ double batch_makespan(const ars_batch* b, int rows) {
   return last;
 }
 
-void choose_rows(ars_batch* b) {
-  b->run_rows = batch_makespan(b, 8) < batch_makespan(b, 4) ? 8 : 4;
-  b->run_zc.resize(b->n);
-  for (int k = 0; k < b->n; ++k) b->run_zc[k] = ars::batch_default_zc(b->P[k], b->run_rows);
-}
-
 void drop_graph(ars_batch* b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
   b->exec = nullptr;
   b->graph = nullptr;
   b->captured = false;
+}
+
+// The tiling of a batch whose caller has set none, for the present device: into
+// rows and zc, as a caller's would be.
+void choose_tiling(ars_batch* b) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
+  const int rows = batch_makespan(b, 8, cus) < batch_makespan(b, 4, cus) ? 8 : 4;
+  if (rows == b->rows) return;  // zc holds that many rows' chunks
+  b->rows = rows;
+  for (int k = 0; k < b->n; ++k) b->zc[k] = ars::batch_default_zc(b->P[k], rows);
+  drop_graph(b);
 }
 
 }  // namespace
@@ -255,6 +263,7 @@ int ars_batch_create(int n_inst, const ars_config* cfgs, ars_batch** out) {
   if (!b) return ARS_ENOMEM;
   b->n = n_inst;
   b->rows = 4;
+  b->chosen = false;
   b->graph = nullptr;
   b->exec = nullptr;
   b->captured = false;
@@ -276,7 +285,6 @@ int ars_batch_create(int n_inst, const ars_config* cfgs, ars_batch** out) {
   std::iota(b->order.begin(), b->order.end(), 0);
   std::stable_sort(b->order.begin(), b->order.end(),
                    [&](int a, int c) { return b->P[a].ncell > b->P[c].ncell; });
-  choose_rows(b);
   *out = b;
   return ARS_OK;
 }
@@ -306,8 +314,7 @@ int ars_batch_set_tiling(ars_batch* b, int rows, const int* zc) {
   }
   b->rows = rows;
   for (int k = 0; k < b->n; ++k) b->zc[k] = zc ? zc[k] : ars::batch_default_zc(b->P[k], rows);
-  b->run_rows = b->rows;
-  b->run_zc = b->zc;
+  b->chosen = true;
   drop_graph(b);
   return ARS_OK;
 }
@@ -322,7 +329,13 @@ int ars_batch_get_tiling(const ars_batch* b, int* rows, int* zc) {
 
 int ars_batch_bind(ars_batch* b, double* d_states, double* d_tmps, void* d_table, void* stream) {
   if (!b || !d_states || !d_tmps || !d_table) return ARS_EINVAL;
-  std::vector<char> h(table_bytes(b->n), 0);
+  std::vector<char> h;
+  try {
+    if (!b->chosen) choose_tiling(b);
+    h.resize(table_bytes(b->n), 0);
+  } catch (const std::bad_alloc&) {
+    return ARS_ENOMEM;
+  }
   ars::BatchInst* insts = (ars::BatchInst*)h.data();
   ars::Params* params = (ars::Params*)(h.data() + params_offset(b->n));
   for (int k = 0; k < b->n; ++k) {
@@ -334,7 +347,7 @@ int ars_batch_bind(ars_batch* b, double* d_states, double* d_tmps, void* d_table
     I.dt = 0.0;
     I.fault_cell = ~0ull;
     I.nxs = ars::batch_segments(b->P[k]);
-    I.zc = b->run_zc[k];
+    I.zc = b->zc[k];
     I.lm = b->P[k].low_mach;
     I.diss = b->P[k].diss;
     I.nc = b->P[k].nc;

@@ -125,8 +125,7 @@ struct ars_batch {
   std::vector<ars_config> cfg;
   std::vector<ars::Params> P;
   std::vector<int> zc;        // vertical chunks per instance
-  int run_rows;               // what the launch takes: rows and zc once the caller or the tuner chose
-  std::vector<int> run_zc;    // them, the library's own choice until then
+  bool chosen;                // rows and zc are the caller's or the tuner's, else ars_batch_bind chooses them
   std::vector<size_t> off;    // state offsets (doubles)
   std::vector<int> order;     // largest first
   size_t total;

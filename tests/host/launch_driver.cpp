@@ -190,12 +190,50 @@ int failed_step() {
   return bad;
 }
 
+// The tiling that the query reports is the one that the launch takes: its rows
+// are the workgroup's, and setting it again changes neither the workgroup nor
+// the table.
+int batch_tiling() {
+  int bad = 0;
+  bool seen[2] = {false, false};
+  std::vector<ars_config> mixed, one = {rb2d(64, 32), rb2d(64, 32), rb2d(64, 32)}, wide(700, rb2d(20, 12));
+  for (int k = 0; k < 96; ++k) mixed.push_back(k % 3 == 0 ? rb2d(64, 32) : k % 3 == 1 ? rb2d(128, 64) : rb2d(256, 128));
+  for (const auto& cfgs : {one, mixed, wide}) {
+    for (int cus : {256, 32, 4}) {
+      num_cu = cus;
+      ars_batch* b = nullptr;
+      if (ars_batch_create((int)cfgs.size(), cfgs.data(), &b) != ARS_OK) return 1;
+      std::vector<double> U(1), T(1);  // addresses only
+      std::vector<char> t1(ars_batch_table_bytes(b)), t2(t1.size());
+      std::vector<int> zc(cfgs.size());
+      int rows = 0;
+      auto launch = [&](std::vector<char>& table) {
+        last_block = 0;
+        if (ars_batch_bind(b, U.data(), T.data(), table.data(), nullptr) != ARS_OK ||
+            ars_batch_step(b, table.data(), 1, nullptr) != ARS_OK)
+          return -1;
+        return (int)last_block / 64;
+      };
+      const int ran = launch(t1);
+      bool ok = ars_batch_get_tiling(b, &rows, zc.data()) == ARS_OK && rows == ran;
+      ok = ok && ars_batch_set_tiling(b, rows, zc.data()) == ARS_OK && launch(t2) == ran && t1 == t2;
+      seen[rows == 8] = true;
+      if (!ok) ++bad;
+      std::printf("%d instances, %d CUs: reported %d rows, launched %d, the same table when set: %d\n", (int)cfgs.size(),
+                  cus, rows, ran, (int)(t1 == t2));
+      ars_batch_destroy(b);
+    }
+  }
+  return bad + !(seen[0] && seen[1]);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   int bad = 1;
   if (what == "failed_step") bad = failed_step();
+  if (what == "batch_tiling") bad = batch_tiling();
   std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
   return bad ? 1 : 0;
 }
