@@ -110,22 +110,21 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 Shares shares_of(long long tiles, int nz, long long most, long long least, int halo) {
   const long long total = tiles * nz;
-  Shares a{};
-  a.groups = (unsigned)std::max(1ll, std::min((total + least - 1) / least, most));
-  a.chunks = a.groups;
-  a.share = (unsigned)(total / a.groups);
-  a.extra = (unsigned)(total % a.groups);
-  const long long longest = a.share + (a.extra ? 1 : 0);
-  const bool aligned = a.extra == 0 && (nz % longest == 0 || longest % nz == 0);
+  auto run = [](long long groups, long long chunks, long long pairs) {
+    Shares s{};
+    s.groups = (unsigned)groups;
+    s.chunks = (unsigned)chunks;
+    s.share = (unsigned)(pairs / chunks);
+    s.step = (unsigned)((((pairs % chunks) << 32) + chunks - 1) / chunks);
+    return s;
+  };
+  const long long g = std::max(1ll, std::min((total + least - 1) / least, most));
+  const long long longest = (total + g - 1) / g;
+  const bool aligned = total % g == 0 && (nz % longest == 0 || longest % nz == 0);
   const long long marches = aligned ? (longest + nz - 1) / nz : 1 + (longest + nz - 2) / nz;
   const long long c = std::min((long long)nz, std::min(most / tiles, std::max(1ll, nz / least)));
-  if (c < 1 || (nz + c - 1) / c + halo > longest + halo * marches) return a;
-  Shares b{};
-  b.groups = (unsigned)(tiles * c);
-  b.chunks = (unsigned)c;
-  b.share = (unsigned)(nz / c);
-  b.extra = (unsigned)(nz % c);
-  return b;
+  if (c < 1 || (nz + c - 1) / c + halo > longest + halo * marches) return run(g, g, total);
+  return run(tiles * c, c, nz);
 }
 
 // Resident workgroups per CU of one kernel.

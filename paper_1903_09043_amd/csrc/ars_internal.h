@@ -10,13 +10,16 @@
 namespace ars {
 
 // How the (tile, plane) pairs of a march along the vertical axis are shared
-// out: workgroup w takes chunk w % chunks of a run of tiles, `share` pairs,
-// the first `extra` chunks one more.  Whole: one run over all tiles (chunks =
-// groups), so every share is equal, but one that crosses from a tile to the
-// next starts a second march with its halo planes.  By tile: every tile is a
-// run of its own, no share crosses, the last chunk of a tile is shorter.
+// out: workgroup w takes chunk w % chunks of a run of tiles, `share` pairs, and
+// the chunks over which the run's remainder spreads one more: `step` is the
+// remainder over the chunks as a 32-bit fraction, rounded up, so that chunk j
+// starts at exactly floor(j remainder / chunks) behind j share (while chunks <
+// 2^16).  Whole: one run over all tiles (chunks = groups), so every share is
+// equal, but one that crosses from a tile to the next starts a second march
+// with its halo planes.  By tile: every tile is a run of its own, no share
+// crosses.
 struct Shares {
-  unsigned groups, chunks, share, extra;
+  unsigned groups, chunks, share, step;
 };
 
 // The schedule whose longest share marches fewer planes, halo planes of every

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/ars.h"
+#include "../../paper_1903_09043_amd/csrc/ars_fused.h"
 #include "../../paper_1903_09043_amd/csrc/ars_internal.h"
 
 namespace {
@@ -227,6 +228,53 @@ int batch_tiling() {
   return bad + !(seen[0] && seen[1]);
 }
 
+// The shares of a march's (tile, plane) pairs: every pair once, in order; and
+// laid end to end over the tiles they are those of floor(w total / groups), so
+// that no workgroup marches more planes, halo planes included, than with those.
+int shares() {
+  int bad = 0, whole = 0, by_tile = 0;
+  auto planes = [](long long a, long long b, int nz, int halo) {
+    long long c = 0;
+    while (a < b) {
+      const long long n = std::min<long long>(nz - a % nz, b - a);
+      c += n + halo;
+      a += n;
+    }
+    return c;
+  };
+  for (long long tiles : {1, 2, 7, 63, 208, 256, 257, 666, 832, 1000})
+    for (int nz : {1, 2, 3, 4, 5, 7, 33, 67, 256, 1000})
+      for (long long most : {1, 8, 255, 256, 1024, 8192})
+        for (long long least : {1, 4, 37})
+          for (int halo : {2, 4}) {
+            const ars::Shares sh = ars::shares_of(tiles, nz, most, least, halo);
+            const long long total = tiles * nz, G = sh.groups;
+            long long at = 0, busiest = 0, even = 0;
+            bool ok = G >= 1 && G <= most;
+            for (long long w = 0; w < G && ok; ++w) {
+              unsigned cur, stop;
+              ars::share_of(sh, (unsigned)w, (unsigned)nz, cur, stop);
+              ok = cur == at && stop > cur && stop <= total;
+              at = stop;
+              busiest = std::max(busiest, planes(cur, stop, nz, halo));
+              even = std::max(even, planes(total * w / G, total * (w + 1) / G, nz, halo));
+            }
+            ok = ok && at == total;
+            if (sh.chunks == G) {
+              ++whole;
+              ok = ok && busiest <= even;
+            } else {
+              ++by_tile;
+            }
+            if (!ok) {
+              if (++bad <= 10)
+                std::printf("%lld tiles of %d planes, %lld workgroups of at most %lld: up to %lld planes against %lld\n", tiles,
+                            nz, G, most, busiest, even);
+            }
+          }
+  return bad + !(whole && by_tile);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -234,6 +282,7 @@ int main(int argc, char** argv) {
   int bad = 1;
   if (what == "failed_step") bad = failed_step();
   if (what == "batch_tiling") bad = batch_tiling();
+  if (what == "shares") bad = shares();
   std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
   return bad ? 1 : 0;
 }
