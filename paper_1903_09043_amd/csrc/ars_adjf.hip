@@ -93,11 +93,6 @@ static Shares adjf_shares(const Params& P, int EX, int EY, int halo) {
   return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo);
 }
 
-// Share of workgroup b: workgroups are dealt to the 8 XCDs in turn, so the
-// shares of one XCD are made consecutive (neighbours in space, whose halo
-// re-reads then hit that XCD's L2).
-__device__ __forceinline__ int xcd_share(int b, int G) { return (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b; }
-
 size_t adjf_workspace_bytes(const Params& P) {
   return (size_t)AF_NF * (size_t)P.ncell * sizeof(double) + 2 * 1024 * sizeof(double);
 }

@@ -41,6 +41,17 @@ struct FusedLayout<2> {  // no LDS fields
   static constexpr int XA = 0, V = 0, DZ = 0, F = 0, B = 0, GX = 0, TOTAL = 0;
 };
 
+// Share of workgroup b of G: workgroups are dealt to the 8 XCDs in turn, so the
+// shares of one XCD are made consecutive (neighbours in space, whose halo
+// re-reads meet in that XCD's L2), for any G: chunks within a tile seldom make
+// a multiple of 8.  Adjoint step, us, such G in launch order and so: 96 x 128 x
+// 256 (234 workgroups) 707, 700; 34 x 255 x 124 315, 310; 101 x 83 x 67 143,
+// 140; 2D 2048 x 1024 164, 158.
+__host__ __device__ __forceinline__ unsigned xcd_share(unsigned b, unsigned G) {
+  const unsigned x = b % 8, r = G % 8;
+  return x * (G / 8) + (x < r ? x : r) + b / 8;
+}
+
 // First pair of workgroup `lw` in the pairs laid end to end (tile-major), and
 // one past its last: 32-bit words (there are at most 2^31 pairs) and one
 // 32-bit division, where 64-bit quotients were 400 scalar instructions in

@@ -57,7 +57,9 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
   // (tile, plane) pairs; those of one XCD are neighbours in space, so halo
   // re-reads hit that XCD's L2.
   const unsigned G = gridDim.x, b = blockIdx.x;
-  const unsigned lw = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  // 2D: other G in launch order (7000 segments x planes, steps with the copy
+  // of an odd count behind them: 27.9 us, 29.3 by XCD)
+  const unsigned lw = DIM == 3 || G % 8 == 0 ? xcd_share(b, G) : b;
   unsigned cur, stop;
   share_of(io.shares, lw, (unsigned)P.nz, cur, stop);
   double lmax = 0.0;

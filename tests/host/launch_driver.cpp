@@ -275,6 +275,22 @@ int shares() {
   return bad + !(whole && by_tile);
 }
 
+// Every share has one workgroup, and those of an XCD (workgroups are dealt to
+// the eight in turn) are one run of consecutive shares, for any count.
+int placement() {
+  int bad = 0;
+  for (unsigned G = 1; G <= 3000; ++G) {
+    std::vector<int> taken(G, 0);
+    bool ok = true;
+    for (unsigned b = 0; b < G; ++b) {
+      const unsigned w = ars::xcd_share(b, G);
+      ok = ok && w < G && !taken[w]++ && (b < 8 || w == ars::xcd_share(b - 8, G) + 1);
+    }
+    if (!ok && ++bad <= 5) std::printf("%u workgroups\n", G);
+  }
+  return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -283,6 +299,7 @@ int main(int argc, char** argv) {
   if (what == "failed_step") bad = failed_step();
   if (what == "batch_tiling") bad = batch_tiling();
   if (what == "shares") bad = shares();
+  if (what == "placement") bad = placement();
   std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
   return bad ? 1 : 0;
 }
