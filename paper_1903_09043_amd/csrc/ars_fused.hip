@@ -38,19 +38,46 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
   constexpr int NW = (NPOS + 63) / 64;  // waves (the last one partial if 64 does not divide NPOS)
 
   const int tid = threadIdx.x;
-  // time step of this step: loaded here, used behind the first state loads
+  // Time step of this step.  2D: loaded here and used behind the first state
+  // loads, t and the log written behind the march, whose latency is the step's.
+  // 3D: all of that first, and dt / dx in scalar registers: the 3D march has no
+  // vector registers to spare (10 spilled with the loads in flight together, 7
+  // with the time step first, 6 so).  us a step with a given dt, in that order:
+  // 8^3 13.5, 12.8, 13.0; 32^3 13.9, 13.4, 13.3; 128^3 103.2, 102.3, 101.9; 512 x
+  // 512 x 4 75.8, 75.2, 74.1.
   RateLoad rate{};
   double dt_given = 0.0;
   if (io.rate_in)
     rate.load(io.rate_in);
   else
     dt_given = *io.dt_in;
-  double dt = 0.0;
-  auto lam_of = [&](double& lamx, double& lamy, double& lamz) __attribute__((always_inline)) {
+  double dt = 0.0, lam[3] = {0.0, 0.0, 0.0};
+  auto take_dt = [&]() __attribute__((always_inline)) {
     dt = io.rate_in ? P.cfl / rate.max() : dt_given;
-    lamx = dt / P.dx[0];
-    lamy = (DIM == 3) ? dt / P.dx[1] : 0.0;
-    lamz = dt / P.dx[2];
+    lam[0] = dt / P.dx[0];
+    lam[1] = (DIM == 3) ? dt / P.dx[1] : 0.0;
+    lam[2] = dt / P.dx[2];
+  };
+  auto book = [&]() __attribute__((always_inline)) {
+    if (blockIdx.x != 0) return;
+    static_assert(NPOS >= RATE_WORDS, "one thread clears one word");
+    if (io.clear_slot && tid < RATE_WORDS) io.clear_slot->w[tid] = 0ull;
+    if (tid == 0) {
+      if (io.t) *io.t = *io.t + dt;
+      if (io.dt_log) *io.dt_log = dt;
+    }
+  };
+  if (DIM == 3) {
+    take_dt();
+    book();
+#pragma unroll
+    for (int a = 0; a < 3; ++a) lam[a] = lane_value(lam[a], 0);
+  }
+  auto lam_of = [&](double& lamx, double& lamy, double& lamz) __attribute__((always_inline)) {
+    if (DIM == 2) take_dt();
+    lamx = lam[0];
+    lamy = lam[1];
+    lamz = lam[2];
   };
 
   // Persistent schedule: every workgroup takes one contiguous share of the
@@ -74,14 +101,7 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
     march_tile<DIM, LM, DISS, NC, EX, EY, SPLIT>(P, Uin, Uout, sm, tx, ty, 0, z0, z1, lam_of, lmax, badcell);
   }
 
-  if (b == 0) {
-    static_assert(NPOS >= RATE_WORDS, "one thread clears one word");
-    if (io.clear_slot && tid < RATE_WORDS) io.clear_slot->w[tid] = 0ull;
-    if (tid == 0) {
-      if (io.t) *io.t = *io.t + dt;
-      if (io.dt_log) *io.dt_log = dt;
-    }
-  }
+  if (DIM == 2) book();
 
   // ---- workgroup reduction of the new-state rate, fault latch --------------
   if (badcell != ~0ull) {
