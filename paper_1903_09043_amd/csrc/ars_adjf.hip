@@ -90,7 +90,7 @@ static int adjf_num_cu() {
 // compute unit, at most 1024 so that the mu/kappa partials of V fit their
 // slots.
 static Shares adjf_shares(const Params& P, int EX, int EY, int halo) {
-  return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo);
+  return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo, true);
 }
 
 size_t adjf_workspace_bytes(const Params& P) {

@@ -55,14 +55,19 @@ __host__ __device__ __forceinline__ unsigned xcd_share(unsigned b, unsigned G) {
 // First pair of workgroup `lw` in the pairs laid end to end (tile-major), and
 // one past its last: 32-bit words (there are at most 2^31 pairs) and one
 // 32-bit division, where 64-bit quotients were 400 scalar instructions in
-// front of the first load.  The longer shares are spread (one high product
-// each): with all of them in front, those of 17 pairs met the same offsets in
-// their tiles and the first XCDs (adjoint step of 512 x 512 x 5: 321 us
-// spread, 337 in front).
+// front of the first load.  3D marches spread the longer shares (one high
+// product each): with all of them in front, those of 17 pairs met the same
+// offsets in their tiles and the first XCDs (adjoint step of 512 x 512 x 5: 322
+// us spread, 337 in front).  The one-wave workgroups of a 2D step are many a
+// CU, and gain by equal neighbours instead (60 x 8200: 15.8 us spread, 14.9 in
+// front; 2048^2 inviscid: 57.5, 56.5).
 __host__ __device__ __forceinline__ void share_of(const Shares& sh, unsigned lw, unsigned nz, unsigned& cur,
                                                   unsigned& stop) {
   const unsigned run = lw / sh.chunks, j = lw - run * sh.chunks;
-  auto before = [&](unsigned k) { return k * sh.share + (unsigned)(((unsigned long long)k * sh.step) >> 32); };
+  auto before = [&](unsigned k) {
+    const unsigned more = (unsigned)(((unsigned long long)k * sh.step) >> 32);
+    return k * sh.share + (more < sh.extra ? more : sh.extra);
+  };
   cur = run * nz + before(j);
   stop = run * nz + before(j + 1);
 }

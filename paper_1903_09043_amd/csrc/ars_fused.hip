@@ -130,14 +130,15 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 // Host-side launch
 // --------------------------------------------------------------------------
-Shares shares_of(long long tiles, int nz, long long most, long long least, int halo) {
+Shares shares_of(long long tiles, int nz, long long most, long long least, int halo, bool spread) {
   const long long total = tiles * nz;
   auto run = [](long long groups, long long chunks, long long pairs) {
     Shares s{};
     s.groups = (unsigned)groups;
     s.chunks = (unsigned)chunks;
     s.share = (unsigned)(pairs / chunks);
-    s.step = (unsigned)((((pairs % chunks) << 32) + chunks - 1) / chunks);
+    s.extra = (unsigned)(pairs % chunks);
+    s.step = spread ? (unsigned)((((pairs % chunks) << 32) + chunks - 1) / chunks) : ~0u;
     return s;
   };
   const long long g = std::max(1ll, std::min((total + least - 1) / least, most));
@@ -190,7 +191,8 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
   // at most as many workgroups as are resident at once
   const long long tiles = (long long)io.ntx * io.nty;
   auto shares = [&](int occ) {
-    return shares_of(tiles, P.nz, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu, least, 4);
+    return shares_of(tiles, P.nz, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu, least, 4,
+                     DIM == 3);
   };
   io.shares = shares(resident<DIM, LM, DISS, NC, EX, EY, false>());
   // the split march where a share has enough steady planes (2D, us a step

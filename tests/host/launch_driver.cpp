@@ -228,9 +228,10 @@ int batch_tiling() {
   return bad + !(seen[0] && seen[1]);
 }
 
-// The shares of a march's (tile, plane) pairs: every pair once, in order; and
-// laid end to end over the tiles they are those of floor(w total / groups), so
-// that no workgroup marches more planes, halo planes included, than with those.
+// The shares of a march's (tile, plane) pairs: every pair once, in order, none
+// longer than another by more than one pair; and spread, laid end to end over
+// the tiles, they are those of floor(w total / groups), so that no workgroup
+// marches more planes, halo planes included, than with those.
 int shares() {
   int bad = 0, whole = 0, by_tile = 0;
   auto planes = [](long long a, long long b, int nz, int halo) {
@@ -246,21 +247,23 @@ int shares() {
     for (int nz : {1, 2, 3, 4, 5, 7, 33, 67, 256, 1000})
       for (long long most : {1, 8, 255, 256, 1024, 8192})
         for (long long least : {1, 4, 37})
-          for (int halo : {2, 4}) {
-            const ars::Shares sh = ars::shares_of(tiles, nz, most, least, halo);
+          for (int form = 0; form < 4; ++form) {
+            const int halo = form & 1 ? 2 : 4;
+            const bool spread = form & 2;
+            const ars::Shares sh = ars::shares_of(tiles, nz, most, least, halo, spread);
             const long long total = tiles * nz, G = sh.groups;
             long long at = 0, busiest = 0, even = 0;
             bool ok = G >= 1 && G <= most;
             for (long long w = 0; w < G && ok; ++w) {
               unsigned cur, stop;
               ars::share_of(sh, (unsigned)w, (unsigned)nz, cur, stop);
-              ok = cur == at && stop > cur && stop <= total;
+              ok = cur == at && stop > cur && stop <= total && stop - cur - sh.share <= 1u;
               at = stop;
               busiest = std::max(busiest, planes(cur, stop, nz, halo));
               even = std::max(even, planes(total * w / G, total * (w + 1) / G, nz, halo));
             }
             ok = ok && at == total;
-            if (sh.chunks == G) {
+            if (sh.chunks == G && spread) {
               ++whole;
               ok = ok && busiest <= even;
             } else {
