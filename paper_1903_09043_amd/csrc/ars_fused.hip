@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 Shares shares_of(long long tiles, int nz, long long most, long long least, int halo, bool spread) {
   const long long total = tiles * nz;
-  auto run = [](long long groups, long long chunks, long long pairs) {
+  auto run = [spread](long long groups, long long chunks, long long pairs) {
     Shares s{};
     s.groups = (unsigned)groups;
     s.chunks = (unsigned)chunks;
