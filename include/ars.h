@@ -152,7 +152,7 @@ int ars_workspace_init(ars_ctx* ctx, void* d_work, void* stream);
  * default, set by ars_create from the grid: in 3D about 1536 (tile, chunk)
  * shares; in 2D a share of about sqrt(segments x planes) / 13 planes (one
  * plane for small grids, whose step time is the latency of one march),
- * of which a launch may take less (1 to 4 planes) until a share is set. */
+ * of which a launch may take less until a share is set. */
 int ars_set_zchunk(ars_ctx* ctx, int zchunk);
 int ars_get_zchunk(const ars_ctx* ctx);
 

@@ -90,7 +90,7 @@ static int adjf_num_cu() {
 // compute unit, at most 1024 so that the mu/kappa partials of V fit their
 // slots.
 static Shares adjf_shares(const Params& P, int EX, int EY, int halo) {
-  return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo, true);
+  return shares_of(adjf_tiles(P, EX, EY, halo), P.nz, std::min(adjf_num_cu(), 1024), 1, 2 * halo);
 }
 
 size_t adjf_workspace_bytes(const Params& P) {
@@ -614,7 +614,7 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_a(Params P, AdjIOF io) {
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
   const int b = blockIdx.x;
   unsigned cur, stop;
-  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
+  share_of<true>(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   while (cur < stop) {
     const int tile = (int)(cur / (unsigned)P.nz);
     const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);
@@ -966,7 +966,7 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_v(Params P, AdjIOF io) {
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
   const int b = blockIdx.x;
   unsigned cur, stop;
-  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
+  share_of<true>(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   double mu_acc = 0.0, ka_acc = 0.0;
   while (cur < stop) {
     const int tile = (int)(cur / (unsigned)P.nz);
@@ -1243,7 +1243,7 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_b(Params P, AdjIOF io) {
   const double lx = dt / P.dx[0], ly = dt / P.dx[1], lz = dt / P.dx[2];
   const int b = blockIdx.x;
   unsigned cur, stop;
-  share_of(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
+  share_of<true>(io.shares, xcd_share(b, gridDim.x), (unsigned)P.nz, cur, stop);
   while (cur < stop) {
     const int tile = (int)(cur / (unsigned)P.nz);
     const int z0 = (int)(cur - (unsigned)tile * (unsigned)P.nz);

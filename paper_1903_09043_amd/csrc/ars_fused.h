@@ -61,15 +61,18 @@ __host__ __device__ __forceinline__ unsigned xcd_share(unsigned b, unsigned G) {
 // us spread, 337 in front).  The one-wave workgroups of a 2D step are many a
 // CU, and gain by equal neighbours instead (60 x 8200: 15.8 us spread, 14.9 in
 // front; 2048^2 inviscid: 57.5, 56.5).
+template <bool SPREAD>
 __host__ __device__ __forceinline__ void share_of(const Shares& sh, unsigned lw, unsigned nz, unsigned& cur,
                                                   unsigned& stop) {
   const unsigned run = lw / sh.chunks, j = lw - run * sh.chunks;
-  auto before = [&](unsigned k) {
-    const unsigned more = (unsigned)(((unsigned long long)k * sh.step) >> 32);
-    return k * sh.share + (more < sh.extra ? more : sh.extra);
-  };
-  cur = run * nz + before(j);
-  stop = run * nz + before(j + 1);
+  if (SPREAD) {
+    auto before = [&](unsigned k) { return k * sh.share + (unsigned)(((unsigned long long)k * sh.step) >> 32); };
+    cur = run * nz + before(j);
+    stop = run * nz + before(j + 1);
+  } else {
+    cur = run * nz + j * sh.share + (j < sh.extra ? j : sh.extra);
+    stop = cur + sh.share + (j < sh.extra ? 1u : 0u);
+  }
 }
 
 // Vertical plane resolution: which plane to load and whether it is a wall

@@ -24,6 +24,7 @@
 //  * No MFMA: nothing here is a contraction.
 
 #include <algorithm>
+#include <numeric>
 
 #include "ars_fused.h"
 
@@ -84,11 +85,12 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
   // (tile, plane) pairs; those of one XCD are neighbours in space, so halo
   // re-reads hit that XCD's L2.
   const unsigned G = gridDim.x, b = blockIdx.x;
-  // 2D: other G in launch order (7000 segments x planes, steps with the copy
-  // of an odd count behind them: 27.9 us, 29.3 by XCD)
-  const unsigned lw = DIM == 3 || G % 8 == 0 ? xcd_share(b, G) : b;
+  // 2D: a G that 8 does not divide in launch order; the host avoids it where it
+  // counts (64 x 32: 40 ns of a step's 6.7 us for the few scalar instructions
+  // more; 60 x 7000, with the copy of an odd step count: 27.9 us, 28.8 by XCD)
+  const unsigned lw = DIM == 3 ? xcd_share(b, G) : (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
   unsigned cur, stop;
-  share_of(io.shares, lw, (unsigned)P.nz, cur, stop);
+  share_of<DIM == 3>(io.shares, lw, (unsigned)P.nz, cur, stop);
   double lmax = 0.0;
   unsigned long long badcell = ~0ull;
   while (cur < stop) {
@@ -130,15 +132,15 @@ __global__ void __launch_bounds__(EX* EY) k_step_fused(Params P, const double* _
 // --------------------------------------------------------------------------
 // Host-side launch
 // --------------------------------------------------------------------------
-Shares shares_of(long long tiles, int nz, long long most, long long least, int halo, bool spread) {
+Shares shares_of(long long tiles, int nz, long long most, long long least, int halo) {
   const long long total = tiles * nz;
-  auto run = [spread](long long groups, long long chunks, long long pairs) {
+  auto run = [](long long groups, long long chunks, long long pairs) {
     Shares s{};
     s.groups = (unsigned)groups;
     s.chunks = (unsigned)chunks;
     s.share = (unsigned)(pairs / chunks);
     s.extra = (unsigned)(pairs % chunks);
-    s.step = spread ? (unsigned)((((pairs % chunks) << 32) + chunks - 1) / chunks) : ~0u;
+    s.step = (unsigned)((((pairs % chunks) << 32) + chunks - 1) / chunks);
     return s;
   };
   const long long g = std::max(1ll, std::min((total + least - 1) / least, most));
@@ -180,19 +182,30 @@ static hipError_t launch_fused_t(const Params& P, const double* Uin, double* Uou
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
       ncu = 256;
   }
-  // 2D: up to one wave per SIMD (1024) a share is one plane, since the step
-  // is then the latency of one march; above that up to 4, and beyond some
-  // 12,000 pairs the number of resident waves decides.  Measured (us a step
-  // with shares of 1, 2, 4, 8): 256 x 128: 8.1, 8.4, 10.2, 14.3; 512 x 256:
-  // 12.3, 11.6, 11.6, 15.4; 1024 x 512: 19.6, 19.6, 19.6, 22.5; 1024^2: 24.6,
-  // 24.2, 24.1, 25.2; 2048 x 1024: 42.8, 41.2, 41.5, 41.3
-  long long least = ts.zchunk;
-  if (DIM == 2 && !ts.chosen) least = std::max(1ll, std::min({4ll, least, total / 1024}));
-  // at most as many workgroups as are resident at once
+  // at most as many workgroups as are resident at once.  2D: the step is the
+  // latency of one march and a workgroup is one wave, so there is at most one a
+  // SIMD while that takes no longer shares than the default; above that shares
+  // of up to 4 planes, and beyond some 12,000 pairs the number of resident waves
+  // decides.  Measured, viscous, us a step with a given dt, one wave a SIMD and
+  // the shares that go beyond it: 60 x 1100 7.7, 9.8 (shares of 1); 512 x 256
+  // (2304 pairs) 9.4, 10.3 (2); 60 x 3000 9.4, 13.1 (2); 60 x 4000 10.8, 14.5 (3);
+  // 60 x 5000 12.0, 15.2 (4); 60 x 6000 13.2, 15.0 (4).  Longer shares: 60 x 8000 14.3
+  // with 4 planes and with 8; 1024^2 24.2 with 2, 24.1 with 4, 25.2 with 8
+  const long long simds = 4ll * ncu;
+  const bool own = DIM == 2 && !ts.chosen, alone = own && total <= simds * ts.zchunk;
+  const long long least = alone ? 1 : own ? std::min(4, ts.zchunk) : ts.zchunk;
   const long long tiles = (long long)io.ntx * io.nty;
+  long long cap = simds;
+  if (const long long c = std::min((long long)P.nz, simds / tiles); alone && c > 0) {
+    // chunks a tile that make a multiple of 8 workgroups (those of an XCD are
+    // then neighbours: 512 x 256, 1017 and 1008 workgroups: 10.6, 9.4 us), if
+    // their shares are no longer
+    const long long m = 8 / std::gcd(tiles, 8ll), c8 = c / m * m;
+    if (c8 > 0 && (P.nz + c8 - 1) / c8 == (P.nz + c - 1) / c) cap = tiles * c8;
+  }
   auto shares = [&](int occ) {
-    return shares_of(tiles, P.nz, (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu, least, 4,
-                     DIM == 3);
+    const long long most = (long long)(ts.wg_per_cu > 0 ? ts.wg_per_cu : occ) * ncu;
+    return shares_of(tiles, P.nz, alone ? std::min(most, cap) : most, least, 4);
   };
   io.shares = shares(resident<DIM, LM, DISS, NC, EX, EY, false>());
   // the split march where a share has enough steady planes (2D, us a step

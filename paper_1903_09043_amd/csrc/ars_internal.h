@@ -11,10 +11,10 @@ namespace ars {
 
 // How the (tile, plane) pairs of a march along the vertical axis are shared
 // out: workgroup w takes chunk w % chunks of a run of tiles, `share` pairs, and
-// `extra` chunks, the run's remainder, one more: spread over the run where
-// `step` is extra / chunks as a 32-bit fraction, rounded up, so that chunk j
-// starts at exactly floor(j extra / chunks) behind j share (while chunks <
-// 2^16), or in front (behind chunk 0) where it is all ones.  Whole: one run over all tiles (chunks = groups), so every share is
+// `extra` chunks, the run's remainder, one more: the first ones, or spread over
+// the run with `step`, extra / chunks as a 32-bit fraction rounded up, so that
+// chunk j starts at exactly floor(j extra / chunks) behind j share (while
+// chunks < 2^16).  Whole: one run over all tiles (chunks = groups), so every share is
 // equal, but one that crosses from a tile to the next starts a second march
 // with its halo planes.  By tile: every tile is a run of its own, no share
 // crosses.
@@ -24,8 +24,8 @@ struct Shares {
 
 // The schedule whose longest share marches fewer planes, halo planes of every
 // march counted, with at most `most` workgroups and at least `least` planes a
-// share where a tile has them; the longer ones spread or in front.
-Shares shares_of(long long tiles, int nz, long long most, long long least, int halo, bool spread);
+// share where a tile has them.
+Shares shares_of(long long tiles, int nz, long long most, long long least, int halo);
 
 // Per-launch inputs/outputs of one fused step.
 struct StepIO {

@@ -24,6 +24,7 @@ int fail_at = -1;        // the one that fails
 hipError_t pending = hipSuccess;
 double state_rate = 1.0; // rate of every state that a step kernel writes
 unsigned last_block = 0; // threads of the last k_batch workgroup
+unsigned last_grid = 0;  // workgroups of the last k_step_fused
 int num_cu = 256;
 
 hipError_t op() {
@@ -56,7 +57,7 @@ void clear(ars::Control* c) {
 
 extern "C" {
 
-hipError_t hipLaunchKernel(const void* f, dim3, dim3 block, void** a, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** a, size_t, hipStream_t) {
   const hipError_t e = op();
   if (e != hipSuccess) return e;
   Dl_info info{};
@@ -64,6 +65,7 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3 block, void** a, size_t, hi
   if (name.find("k_step_fused") != std::string::npos) {
     const ars::Params& P = *(const ars::Params*)a[0];
     const ars::StepIO& io = *(const ars::StepIO*)a[3];
+    last_grid = grid.x;
     const double dt = io.rate_in ? P.cfl / largest(io.rate_in) : *io.dt_in;
     if (io.dt_log) *io.dt_log = dt;
     if (io.clear_slot) std::memset(io.clear_slot, 0, sizeof *io.clear_slot);
@@ -250,13 +252,16 @@ int shares() {
           for (int form = 0; form < 4; ++form) {
             const int halo = form & 1 ? 2 : 4;
             const bool spread = form & 2;
-            const ars::Shares sh = ars::shares_of(tiles, nz, most, least, halo, spread);
+            const ars::Shares sh = ars::shares_of(tiles, nz, most, least, halo);
             const long long total = tiles * nz, G = sh.groups;
             long long at = 0, busiest = 0, even = 0;
             bool ok = G >= 1 && G <= most;
             for (long long w = 0; w < G && ok; ++w) {
               unsigned cur, stop;
-              ars::share_of(sh, (unsigned)w, (unsigned)nz, cur, stop);
+              if (spread)
+                ars::share_of<true>(sh, (unsigned)w, (unsigned)nz, cur, stop);
+              else
+                ars::share_of<false>(sh, (unsigned)w, (unsigned)nz, cur, stop);
               ok = cur == at && stop > cur && stop <= total && stop - cur - sh.share <= 1u;
               at = stop;
               busiest = std::max(busiest, planes(cur, stop, nz, halo));
@@ -294,6 +299,38 @@ int placement() {
   return bad;
 }
 
+// A 2D step whose pairs, in shares no longer than the default, give each SIMD
+// at most one workgroup (a wave) never puts two on one, and shares of one plane
+// are left where there are no more pairs than SIMDs.
+int one_wave() {
+  int bad = 0;
+  std::vector<double> work(8192);
+  double d[2] = {1e-3, 1e-3};
+  for (int cus : {256, 64}) {
+    num_cu = cus;
+    for (int nz = 3; nz <= 24 * cus; nz += nz / 23 + 1) {
+      const ars_config cfg = rb2d(60, nz);
+      ars_ctx* x = nullptr;
+      if (ars_create(&cfg, &x) != ARS_OK) return 1;
+      if (ars_workspace_bytes(x) > work.size() * 8) work.resize(ars_workspace_bytes(x) / 8);
+      std::vector<double> A(ars_state_len(x)), B(A.size());
+      const int simds = 4 * cus;
+      if (nz > simds * ars_get_zchunk(x)) {
+        ars_destroy(x);
+        break;
+      }
+      last_grid = 0;
+      const bool ok = ars_step_sched(x, A.data(), B.data(), work.data(), 1, d, nullptr, nullptr) == ARS_OK;
+      if (!ok || (int)last_grid > simds || (nz <= simds && (int)last_grid != nz)) {
+        if (++bad <= 10) std::printf("%d pairs: %u workgroups on %d SIMDs\n", nz, last_grid, simds);
+      }
+      ars_destroy(x);
+    }
+  }
+  num_cu = 256;
+  return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -303,6 +340,7 @@ int main(int argc, char** argv) {
   if (what == "batch_tiling") bad = batch_tiling();
   if (what == "shares") bad = shares();
   if (what == "placement") bad = placement();
+  if (what == "one_wave") bad = one_wave();
   std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
   return bad ? 1 : 0;
 }
