@@ -454,7 +454,8 @@ int ars_batch_read(const ars_batch* b, const void* d_table, double* h_t, double*
  * ars_autotune times the fused step (trial_steps steps after one untimed
  * step, per candidate) for candidate (tile, zchunk, wg_per_cu) triples (both
  * tiles of ars_set_tile3 in 3D) on a copy of d_state, keeps the fastest in
- * ctx and returns it in *out (may be NULL).
+ * ctx and returns it in *out (may be NULL).  In 2D the untuned launch is a
+ * candidate too; where it is kept, zchunk is the default it starts from.
  * d_state is not modified; the workspace's rate slots and fault latch are
  * reset (as by ars_workspace_init).  It allocates and frees a temporary
  * device copy of two states: a set-up call, never to be captured.
@@ -466,8 +467,8 @@ int ars_batch_read(const ars_batch* b, const void* d_table, double* h_t, double*
  * restored to its contents at the call; it allocates a temporary copy.
  *
  * cache_path (may be NULL): text file of tuned shapes, one line per key
- * "<key> <a> <b> <ms_per_step> [<tile>]"; a key found there is applied without
- * timing (from_cache = 1), otherwise the result is appended.  Keys name
+ * "<key> <a> <b> <ms_per_step> [<tile>]" (tile 2: the untuned 2D launch); a
+ * key found there is applied without timing (from_cache = 1), otherwise the result is appended.  Keys name
  * the device (architecture, compute units) and the problem (dimension,
  * grid, boundary kinds, theta and dissipation switches; for a batch a hash
  * of all instances' shapes and switches). */

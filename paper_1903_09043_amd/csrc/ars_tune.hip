@@ -6,8 +6,8 @@
 // shape.  Results never depend on the tiling (every candidate computes the
 // same bits), only time does.
 //
-// Cache file: one entry per line, "<key> <a> <b> <ms_per_step>", later lines
-// winning.  Keys name the device (architecture, compute units) and what
+// Cache file: one entry per line, "<key> <a> <b> <ms_per_step> [<tile>]", later
+// lines winning.  Keys name the device (architecture, compute units) and what
 // determines the kernel's work: dimension, grid, boundary kinds, theta and
 // dissipation switches (step), or a hash of every instance's shape and
 // switches (batch).
@@ -24,6 +24,10 @@
 #include "ars_internal.h"
 
 namespace {
+
+// In the place of a tile: the untuned launch of a 2D step, whose shares no
+// zchunk describes.
+constexpr int OWN_2D = 2;
 
 std::string device_tag() {
   int dev = 0;
@@ -115,12 +119,13 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
   ars_tune_result r{};
   int za = 0, wb = 0, tc = 0;
   double ms = 0.0;
-  if (cache_lookup(cache_path, key, &za, &wb, &ms, &tc) && za >= 1 && wb >= 0 && (tc == 0 || (tc == 1 && P.dim == 3))) {
-    ctx->ts.tile3 = tc;
+  if (cache_lookup(cache_path, key, &za, &wb, &ms, &tc) && za >= 1 && wb >= 0 &&
+      (tc == 0 || (tc == 1 && P.dim == 3) || (tc == OWN_2D && P.dim == 2))) {
+    ctx->ts.tile3 = P.dim == 3 ? tc : 0;
     ctx->ts.zchunk = za;
-    ctx->ts.chosen = true;
+    ctx->ts.chosen = tc != OWN_2D || P.dim == 3;
     ctx->ts.wg_per_cu = wb;
-    r.tile3 = tc;
+    r.tile3 = ctx->ts.tile3;
     r.zchunk = za;
     r.wg_per_cu = wb;
     r.ms_per_step = ms;
@@ -130,7 +135,8 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
   }
   // candidates: the 3D tiles; for each, vertical shares per workgroup
   // around that tile's default; workgroups per CU (0 = as many as are
-  // resident at once, else that many per CU, queued beyond residency)
+  // resident at once, else that many per CU, queued beyond residency); in 2D
+  // also the untuned launch (share 0 below)
   std::vector<int> tiles = {ctx->ts.tile3};
   if (P.dim == 3) tiles = {0, 1};
   std::vector<int> ws = {0, 2, 4};
@@ -150,13 +156,15 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
   for (int tl : tiles) {
     std::vector<int> zs;
     const int z0 = tl == keep.tile3 ? keep.zchunk : ars::default_zchunk(P, tl);
+    if (P.dim == 2) zs.push_back(0);
     for (int z : {z0, 1, 2, 4, 8, 16, 32, 64, std::max(1, z0 / 2), z0 * 2})
       if (z >= 1 && z <= P.nz && std::find(zs.begin(), zs.end(), z) == zs.end()) zs.push_back(z);
     for (int z : zs) {
       for (int w : ws) {
+        if (z == 0 && w != 0) continue;
         ctx->ts.tile3 = tl;
-        ctx->ts.zchunk = z;
-        ctx->ts.chosen = true;
+        ctx->ts.zchunk = z ? z : ars::default_zchunk(P, tl);
+        ctx->ts.chosen = z != 0;
         ctx->ts.wg_per_cu = w;
         // every candidate starts from the caller's state
         if (hipMemcpyAsync(A, d_state, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) rc = ARS_EDEVICE;
@@ -189,7 +197,8 @@ int ars_autotune(ars_ctx* ctx, const double* d_state, void* d_work, int trial_st
     return rc;
   }
   ctx->ts = bestts;
-  cache_store(cache_path, key, bestts.zchunk, bestts.wg_per_cu, best, bestts.tile3);
+  cache_store(cache_path, key, bestts.zchunk, bestts.wg_per_cu, best,
+              P.dim == 2 && !bestts.chosen ? OWN_2D : bestts.tile3);
   r.tile3 = bestts.tile3;
   r.zchunk = bestts.zchunk;
   r.wg_per_cu = bestts.wg_per_cu;

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -25,6 +26,7 @@ hipError_t pending = hipSuccess;
 double state_rate = 1.0; // rate of every state that a step kernel writes
 unsigned last_block = 0; // threads of the last k_batch workgroup
 unsigned last_grid = 0;  // workgroups of the last k_step_fused
+unsigned best_grid = 0;
 int num_cu = 256;
 
 hipError_t op() {
@@ -102,6 +104,30 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
   *n = 8;
+  return hipSuccess;
+}
+
+// A call takes the less time, the nearer its workgroups' number is to best_grid.
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::malloc(n);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void* p) {
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t*) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = 1.0f + (float)std::abs((long)last_grid - (long)best_grid);
+  return hipSuccess;
+}
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
+  std::memset(p, 0, sizeof *p);
+  std::strcpy(p->gcnArchName, "gfx950");
+  p->multiProcessorCount = num_cu;
   return hipSuccess;
 }
 
@@ -331,6 +357,38 @@ int one_wave() {
   return bad;
 }
 
+// Tuning a 2D step whose untuned launch is the fastest leaves that launch, for
+// the context that was tuned and for one that finds it in the cache.
+int tuned_2d(const char* cache) {
+  int bad = 0;
+  for (auto [nx, nz] : {std::pair{512, 256}, {60, 3000}, {64, 32}, {1024, 1024}}) {
+    const ars_config cfg = rb2d(nx, nz);
+    std::vector<double> work(8192), A, B;
+    double d = 1e-3;
+    unsigned grid[3];
+    for (int k = 0; k < 3; ++k) {  // untuned, tuned, from the cache
+      ars_ctx* x = nullptr;
+      if (ars_create(&cfg, &x) != ARS_OK) return 1;
+      work.resize(std::max(work.size(), ars_workspace_bytes(x) / 8 + 1));
+      A.resize(ars_state_len(x));
+      B.resize(A.size());
+      if (ars_workspace_init(x, work.data(), nullptr) != ARS_OK) return 1;
+      ars_tune_result r{};
+      if (k && (ars_autotune(x, A.data(), work.data(), 2, cache, nullptr, &r) != ARS_OK || r.from_cache != (k == 2)))
+        ++bad;
+      if (ars_step_sched(x, A.data(), B.data(), work.data(), 1, &d, nullptr, nullptr) != ARS_OK) return 1;
+      grid[k] = last_grid;
+      if (k == 0) best_grid = last_grid;
+      ars_destroy(x);
+    }
+    if (grid[1] != grid[0] || grid[2] != grid[0]) {
+      ++bad;
+      std::printf("%d x %d: %u workgroups untuned, %u tuned, %u from the cache\n", nx, nz, grid[0], grid[1], grid[2]);
+    }
+  }
+  return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -341,6 +399,7 @@ int main(int argc, char** argv) {
   if (what == "shares") bad = shares();
   if (what == "placement") bad = placement();
   if (what == "one_wave") bad = one_wave();
+  if (what == "tuned_2d" && argc > 2) bad = tuned_2d(argv[2]);
   std::printf(bad ? "FAILED %d\n" : "ok\n", bad);
   return bad ? 1 : 0;
 }

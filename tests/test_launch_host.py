@@ -28,15 +28,16 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["failed_step", "batch_tiling", "shares", "placement", "one_wave"])
-def test_launches(driver, what):
+@pytest.mark.parametrize("what", ["failed_step", "batch_tiling", "shares", "placement", "one_wave", "tuned_2d"])
+def test_launches(driver, what, tmp_path):
     """failed_step: the time steps after a call that ended in an error are
     those of the new call's own states.  batch_tiling: ars_batch_get_tiling
     reports what is launched and bound.  shares: the schedule of a march's
     (tile, plane) pairs takes every pair once and its longest share is no
     longer than that of an even split.  placement: neighbouring shares meet on
     one XCD whatever the number of workgroups.  one_wave: 2D steps that can
-    give every SIMD at most one workgroup do."""
-    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=120)
+    give every SIMD at most one workgroup do.  tuned_2d: tuning keeps the
+    untuned launch of a 2D step where that is the fastest."""
+    r = subprocess.run([driver, what, str(tmp_path / "tune.txt")], capture_output=True, text=True, timeout=120)
     print(r.stdout[-4000:], r.stderr[-2000:])
     assert r.returncode == 0 and r.stdout.strip().endswith("ok")
