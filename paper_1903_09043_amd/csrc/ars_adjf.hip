@@ -1262,13 +1262,14 @@ __global__ void __launch_bounds__(EX* EY) k_adjf_b(Params P, AdjIOF io) {
 // own.  Here one workgroup takes a tile of 12 x 12 cells with the 2-cell halo
 // that the reverse of a cell reaches, one thread per position, and goes
 // through the phases of A, V and B in LDS with a barrier between them: no
-// fields in memory, one launch.  Every face is reversed by the thread of its
+// fields in memory, one launch (and one of 2.6 us for the parameter gradient,
+// where viscosity and the caller ask for it).  Every face is reversed by the thread of its
 // lower cell, which publishes what it owes the others; 36 doubles a position
 // (73.7 KB: two workgroups per CU), the later fields over the earlier ones.
 // A tile's latency bounds it up to 512 tiles, the arithmetic of the halo
-// (16^2 / 12^2) above.  us a call, phase kernels against this (the second is
-// the caller's launch rate up to 256 x 128): 64 x 32: 38, 14; 256 x 128: 46,
-// 15; 512 x 256: 67, 19; 1024 x 512: 206, 53; 2048 x 1024: 725, 175.
+// (16^2 / 12^2) above.  us a call without the parameter gradient, phase kernels
+// against this: 64 x 32: 36, 9.3; 256 x 128: 43, 9.1; 512 x 256: 65, 14; 1024 x
+// 512: 201, 47; 2048 x 1024: 720, 153; with it 256 x 128: 46, 12.5.
 constexpr int A2_E = 16, A2_T = A2_E - 4;
 enum {
   L2_Q = 0,    // ux, uz, T, rc, 1/rc, 1/c, p, rho

@@ -7,8 +7,9 @@
 //    2-cell halo and marches along the vertical (gravity) axis.  The stencil
 //    of one update is the radius-2 diamond (the upwinded transport value
 //    b~ of a neighbour needs all faces of that neighbour), so the halo is 2.
-//  * The vertical neighbours live in registers (a rolling window of planes);
-//    lateral neighbours are exchanged through LDS once per plane:
+//  * The vertical neighbours live in registers (a rolling window of planes).
+//    2D: a row segment is one wave and its neighbours the lanes beside (DPP
+//    moves).  3D: lateral neighbours are exchanged through LDS once per plane:
 //      XA  acoustic fields (rho c, c, p, u_lat) of the newest plane p
 //      V   u, T of plane p-1 (viscous stencil), DZ  u(p) - u(p-2)
 //      F   own +x/+y acoustic faces (u*, Pi*, Pi* u*) of plane p
@@ -19,8 +20,9 @@
 //  * Every face is evaluated once; the only HBM traffic is the read of U^n
 //    and the write of U^{n+1} (plus halo re-reads that hit L2).
 //  * Epilogue: the rate of the NEW state for the next CFL time step is
-//    reduced wave -> LDS -> one atomicMax per workgroup, so dt never leaves
-//    the device and n steps need no host synchronisation.
+//    reduced (one wave: DPP moves; several: LDS) to one atomicMax per
+//    workgroup, spread over 64 words, so dt never leaves the device and n steps
+//    need no host synchronisation.
 //  * No MFMA: nothing here is a contraction.
 
 #include <algorithm>

@@ -76,7 +76,7 @@ struct ImexLayout {
   double* sv;
   double* t;
   double* b;
-  double* r2;       // CG, 2D: the second residual and product of the ping-pong
+  double* r2;       // CG: the second residual and product of the ping-pong
   double* q2;
   double* part;     // partial sums (one per block of a reduction; CG: up to two sets of four)
   double* sc;       // scalars
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(BS) void k_cg_iter_2d(Params P, const double* __res
                                                    double* __restrict__ x, const double* __restrict__ tau,
                                                    const double* __restrict__ irc, const double* __restrict__ irc2,
                                                    const double* __restrict__ pprev, double* __restrict__ pcur,
-                                                   int pstride, double* __restrict__ sc, int it, int wallmask) {
+                                                   int pstride, int it, int wallmask) {
   __shared__ double sP[CP_Z][CP_X];
   __shared__ double sT[CC_Z][CC_X];
   __shared__ double sI[CC_Z][CC_X];
@@ -899,13 +899,6 @@ __global__ __launch_bounds__(C3_T) void k_cg_iter_3d(Params P, const double* __r
   }
 }
 
-// (r, r) of the last fused iteration, for the host's convergence test.
-__global__ __launch_bounds__(BS) void k_cg_check_rr(const double* __restrict__ rr_parts, int nb,
-                                                    double* __restrict__ sc) {
-  const double rr = sum_parts(rr_parts, nb);
-  if (threadIdx.x == 0) sc[SC_CG_CHK] = rr;
-}
-
 // alpha = (r, r) / (p, q), every block adding the block sums of (p, q) in
 // the same order; then x += alpha p, r -= alpha q and the block sums of
 // the new (r, r).
@@ -1088,9 +1081,12 @@ struct Imex {
   // taken, and half a block of CG_CHECK iterations for the late read of the
   // residual.  Time per iteration as measured (with the host's
   // reads): without, 12.9 us at 64^2, 13.2 at 512^2, 27.8 at 1024^2 in 2D and
-  // 13 us at 32^3, 30 at 96^3, 221 at 200^3; with, 68 us at 64^2 (the transforms' launches,
-  // product, updates and a read of the residual), 390 at 1024^2 (330 since the
-  // transforms are half products: near the line the plain iteration is taken).
+  // 13 us at 32^3, 30 at 96^3, 221 at 200^3; with, 68 us at 64^2 (the transforms'
+  // launches, product, updates and a read of the residual), 330 at 1024^2, where
+  // the expression below gives 341: TRIG_RATE counts a transform as the full
+  // product of 2 n flop a value, which its half products do in 52 us (41 TF/s
+  // so counted) where 62 are allowed, so near the line the plain iteration is
+  // taken.  Boxes with ny nz beyond 2^21 have not been run with it.
   bool prefer_trig(const double* h, double red, int max_iter, TrigCoef* tc) const {
     const double n = (double)L.n;
     if (P.nx > TRIG_MAXN || P.ny > TRIG_MAXN || P.nz > TRIG_MAXN || (long long)P.ny * P.nz > (1 << 21) ||
@@ -1198,13 +1194,13 @@ struct Imex {
       const int o = k & 1, in = o ^ 1;
       if (DIM == 2)
         hipLaunchKernelGGL(k_cg_iter_2d, dim3(ga), dim3(BS), 0, s, P, d_dt, R[in], Q[in], Pv[in], R[o], Q[o], Pv[o],
-                           L.x, L.rh, L.sv, L.t, S[in], S[o], ps, L.sc, k, wallmask);
+                           L.x, L.rh, L.sv, L.t, S[in], S[o], ps, k, wallmask);
       else
         hipLaunchKernelGGL(k_cg_iter_3d, dim3(ga), dim3(C3_T), 0, s, P, d_dt, R[in], Q[in], Pv[in], R[o], Q[o],
                            Pv[o], L.x, L.rh, L.sv, L.t, S[in], S[o], ps, k, wallmask, zc);
       it = k + 1 - lead;
       if (it > 0 && (it % CG_CHECK == 0 || it == max_iter)) {
-        hipLaunchKernelGGL(k_cg_check_rr, dim3(1), dim3(BS), 0, s, S[o] + CGS_RR * ps, (int)ga, L.sc);
+        hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(BS), 0, s, S[o] + CGS_RR * ps, (int)ga, L.sc);
         if (read(SC_CG_CHK, &rr) != ARS_OK) return ARS_EDEVICE;
         if (!std::isfinite(rr)) return ARS_ENOCONV;
         if (rr <= target) break;

@@ -39,8 +39,6 @@ namespace ars {
 
 constexpr int SPEC_MAXN = 2048;
 
-__device__ __forceinline__ int fft_wavenumber(int j, int n) { return j < (n + 1) / 2 ? j : j - n; }
-
 // tw[j] = exp(-2 pi i j / n), j < n, cos in tw[0..n), -sin in tw[n..2n).
 __device__ __forceinline__ void fill_twiddles(double* tw, int n) {
   for (int j = threadIdx.x; j < n; j += blockDim.x) {
